@@ -98,6 +98,7 @@ struct ColumnF32 {
   uint32_t nu, nvb;  // tile column and first row (relative to the origin)
   float du, fvb;     // fractions of u and of v(kb)
   float w, dvk;      // W_dis = f^2 and dv/dk
+  float vl, eps;     // v(kb) relative to the origin, and dv/dk - 1
 };
 
 // Hardware reciprocal (1 ulp) and fraction on the GPU; the host build, used
@@ -127,8 +128,10 @@ __host__ __device__ __forceinline__ ColumnF32 column_f32(const BrickView& b, flo
   c.du = fract_f32(ul);
   c.nvb = static_cast<uint32_t>(vl);
   c.fvb = fract_f32(vl);
+  c.vl = vl;
   c.w = f * f;
   c.dvk = kvf * f;
+  c.eps = fmaf(kvf, f, -1.0f);
   return c;
 }
 
@@ -151,8 +154,10 @@ __device__ __forceinline__ ColumnF32 column_f64(const GeoConst& gc, const ViewGe
   c.du = static_cast<float>(ul - fu);
   c.nvb = static_cast<uint32_t>(fv);
   c.fvb = static_cast<float>(vl - fv);
+  c.vl = static_cast<float>(vl);
   c.w = static_cast<float>(f * f);
   c.dvk = static_cast<float>(gc.kv * f);
+  c.eps = static_cast<float>(gc.kv * f - 1.0);
   return c;
 }
 

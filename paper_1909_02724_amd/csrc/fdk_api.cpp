@@ -347,11 +347,7 @@ fdk_status fdk_backproject(const fdk_geometry* g, int32_t view0, int32_t nviews,
     for (int32_t s = 0; s < vb.nviews; ++s) fdk::set_view(&vb, s, g->angles[view0 + b + s]);
     const char* qb = static_cast<const char*>(q) + (size_t)b * vstride * dtype_size(q_dtype);
     for (const fdk::SliceRun& r : sl.runs) {
-      const fdk::TileShape ts =
-          r.mirror ? fdk::tile_shape(g, gc, r, vb, fdk::kBrickZ, fdk::kTileEntryBytes,
-                                     fdk::kPrefetchSlots, direct, true, true)
-                   : fdk::tile_shape(g, gc, r, vb, fdk::kPlainBrickZ, fdk::kPlainEntryBytes,
-                                     fdk::kPlainPrefetchSlots, direct, true);
+      const fdk::TileShape ts = fdk::bp_tile_shape(g, gc, r, vb, direct);
       if (int e = fdk::launch_backproject(gc, r, vb, ts, qb, q_dtype, vstride, vol, scale,
                                           (b > 0) || acc0, stream))
         return fail(FDK_ERR_HIP, "back-projection launch failed: HIP error %d", e);

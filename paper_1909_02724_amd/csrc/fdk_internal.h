@@ -77,7 +77,8 @@ struct ViewBatch {
 // kBrickX x kBrickY columns and kBrickZ consecutive slices of a slice run
 // (plus their mirrors for a mirrored run). In the tiled variant it stages
 // the brick's detector footprint for each view, a tile of tu x tv pixels,
-// into LDS, vc views at a time. tu and tv are host-side upper bounds.
+// into LDS, vc views at a time (the staged kernel: two tiles in turn; bricks
+// of small volumes hold 8 or 4 slices). tu and tv are host-side upper bounds.
 constexpr int kBrickX = 16;
 constexpr int kBrickY = 16;
 constexpr int kBrickZ = 16;
@@ -85,11 +86,12 @@ constexpr int kBrickThreads = kBrickX * kBrickY;
 constexpr int kWaveLanes = 64;
 // Occupancy decides the back-projector's speed more than staging depth
 // does (measured on MI355X): five 256-thread workgroups per CU, hence at
-// most 27.5 KB of tiles (with the 4.5 KB of per-view brick constants, 32 KB
-// a workgroup) and 102 VGPRs, with two views per stage, run 5 %
-// faster than four with three views (and four with three 11 % (FP32) to
-// 47 % (FP16) faster than three with four). The adjoint stages up to three
-// views in 35.5 KB.
+// most 27.4 KB of tiles (with the 4.5 KB of per-view brick constants, 32 KB
+// a workgroup) and 102 VGPRs, with two tiles, run 5 %
+// faster than four with three views a stage (and four with three 11 % (FP32)
+// to 47 % (FP16) faster than three with four; six, at 80 VGPRs and 64 views a
+// launch, spill: 16.1 against 12.7 ms at 512^3). The adjoint stages up to
+// three views in 35.5 KB.
 constexpr int kMaxStageViews = 3;
 constexpr int kBpStageViews = 2;
 constexpr int kPrefetchSlots = 6;       // tile entries a thread prefetches per stage
@@ -97,7 +99,7 @@ constexpr int kPrefetchSlots = 6;       // tile entries a thread prefetches per 
 // staging passes per view) go to a four-wave instance with more slots.
 constexpr int kWidePrefetchSlots = 12;
 constexpr int kTileLdsBytes = 36352;    // LDS budget for the adjoint's and the four-wave tiles
-constexpr int kBpTileLdsBytes = 28160;  // and for the five-wave back-projector's
+constexpr int kBpTileLdsBytes = 28032;  // and for the five-wave back-projector's (27.4 KB)
 constexpr int kTileEntryBytes = 16;     // (q, dq/du) of a row and of its mirror row
 
 struct TileShape {
@@ -105,6 +107,10 @@ struct TileShape {
   int32_t vc;            // views staged at once; 0 selects the direct variant
   int32_t rstep, rows;   // staging: rows advanced per pass, passes per view
   int32_t wide;          // back-projector: the four-wave instance with kWidePrefetchSlots
+  int32_t span;          // slices whose taps lie in span + 2 consecutive rows, at every column (0: none)
+  int32_t np;            // back-projector: slices (pairs) per thread
+  int32_t groups;        // back-projector: 256-thread groups per workgroup (0: the general kernel)
+  int32_t lds_bytes;     // back-projector: dynamic LDS of a workgroup
   int32_t nbx, nby, nseg;  // bricks along x, y and z-segments of the run
   // Adjoint: lane (tx, ty) visits its slots from (rot_a tx + rot_b (ty mod 4))
   // mod 16 on, which spreads the lanes' LDS adds over the banks.
@@ -122,6 +128,25 @@ struct TileShape {
 TileShape tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& run,
                      const ViewBatch& vb, int32_t bz, int32_t entry_bytes, int32_t slots,
                      bool direct, bool bp_staging = false, bool read_pitch = false);
+// Back-projector: brick heights (pairs per thread) and view groups of small
+// volumes, and the row walk; the rules and what they measured are at
+// bp_tile_shape (tiles.cpp) and span_column (bp.hip).
+constexpr int kMidBrickZ = 8;
+constexpr int kSmallBrickZ = 4;
+constexpr int kMaxGroups = 4;  // 256-thread groups sharing a brick, each with its own views
+constexpr int kCus = 256;
+constexpr int kResidentGroups = 4 * kCus;   // groups the chip holds at four waves per SIMD
+constexpr int kGroupLdsBytes = 154 * 1024;  // of 160 KB, beside the per-view brick constants
+// Staging passes of a view's tile: exactly so many in the five-wave kernel, at
+// most so many in the four-wave one.
+constexpr int stage_passes(bool mirror, bool wide) { return mirror ? (wide ? 8 : 3) : (wide ? 14 : 6); }
+// Largest drift of v against rows one apart, in pixels, over the slices of a
+// row walk: under 1, less a margin, so that its first row stays above the
+// tile origin (which has a pixel of margin).
+constexpr double kSpanDrift = 0.95;
+// Tile, brick and workgroup of a back-projection launch.
+TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& run,
+                        const ViewBatch& vb, bool direct);
 // Plain (unmirrored) back-projection runs: 32 slices per brick, the tile
 // holding (q, dq/du) of the main rows only; a prefetch slot holds one row's
 // pair instead of two, so twice as many fit the same registers.

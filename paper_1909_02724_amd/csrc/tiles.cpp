@@ -51,6 +51,9 @@ TileShape tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& 
     // only if their columns are 7 or more apart.
     while (ts.tvp % 16 != 7 && ts.tvp % 16 != 9) ts.tvp += 2;
   }
+  // dv/dk over the volume's columns, z in [d - r, d + r].
+  const double drift = std::fmax(std::fabs(gc.kv / zmin - 1.0), std::fabs(gc.kv / (g->sod + r) - 1.0));
+  ts.span = 7.0 * drift <= kSpanDrift ? 8 : 3.0 * drift <= kSpanDrift ? 4 : 0;
   if (bp_staging) {
     // The back-projector stages a tile row with a group of 32 or 64 lanes
     // (one wave at most): a lane per column and one more.
@@ -68,7 +71,7 @@ TileShape tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& 
     ts.vc = static_cast<int32_t>(std::max<int64_t>(vc, 0));
     return ts;
   }
-  // Back-projector: the five-wave kernel (slots prefetch slots, 27.5 KB of
+  // Back-projector: the five-wave kernel (slots prefetch slots, 27.4 KB of
   // tiles) when it stages all kBpStageViews views per stage, else the
   // four-wave one (more slots and 35.5 KB) if that stages more.
   const int64_t vc5 = std::min<int64_t>({kBpStageViews, kBpTileLdsBytes / per_view, slots / ts.rows});
@@ -76,6 +79,64 @@ TileShape tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& 
   const int64_t vc4 = std::min<int64_t>({kBpStageViews, kTileLdsBytes / per_view, wide_slots / ts.rows});
   ts.wide = vc5 < kBpStageViews && vc4 > vc5;
   ts.vc = static_cast<int32_t>(std::max<int64_t>(ts.wide ? vc4 : vc5, 0));
+  return ts;
+}
+
+// Brick height, kernel and workgroup of a back-projection launch.
+//
+// Bricks of 16 slices (pairs) a thread stage the fewest pixels per voxel, so
+// large volumes take them, one 256-thread group a brick. Up to 1024 bricks
+// are all resident at once, and a view's chain of loads, barrier and column
+// sums is latency: there
+//  - bricks shrink to 8 or 4 slices while they number at most one a CU
+//    (96^3 from 90 views: 59 us at 16 slices, 71 at 4 (432 bricks), 46 at 8
+//    (216); 80^3: 50 at 16, 39 at 4; 64^3 from 64 views: 91 -> 31 with groups);
+//  - groups of threads share a brick's views: 4 up to a brick a CU, which
+//    fills it with 16 waves (128^3 from 180 views, 256 bricks: 238 -> 119 us,
+//    147 with two), 2 up to 1.5 (500 bricks: 192 us with one, 201 with two;
+//    864 bricks: 306 with one, 380 with two, which no longer fit at once).
+// Tiles of which two do not fit the 35.5 KB of a quarter of a CU's LDS: plain
+// runs take the staged kernel all the same (301 x 277 x 199 at 1.2 pixels a
+// voxel: 2.08 -> 1.72 ms), small mirrored grids bricks of 8 slices (450
+// bricks: 690 us general, 559 at 16 slices, 528 at 8), and large mirrored
+// grids the general kernel (400^3, wide cone: 4.0 ms, staged 4.1 at 16 slices
+// and 4.8 at 8).
+TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& run,
+                        const ViewBatch& vb, bool direct) {
+  const int32_t entry = run.mirror ? kTileEntryBytes : kPlainEntryBytes;
+  auto shape = [&](int32_t np) {
+    TileShape t = tile_shape(g, gc, run, vb, run.mirror ? np : 2 * np, entry,
+                             run.mirror ? kPrefetchSlots : kPlainPrefetchSlots, direct, true,
+                             run.mirror != 0);
+    t.np = np;
+    t.lds_bytes = t.vc * t.tu * t.tvp * entry;
+    return t;
+  };
+  // Dynamic LDS of n groups: two tiles each, and at the end their sums.
+  auto lds = [&](const TileShape& t, int32_t n) {
+    return std::max(2 * n * t.tu * t.tvp * entry,
+                    (n - 1) * t.np * kBrickThreads * static_cast<int32_t>(sizeof(float)));
+  };
+  auto bricks = [](const TileShape& t) { return static_cast<int64_t>(t.nbx) * t.nby * t.nseg; };
+  auto staged = [&](const TileShape& t) {
+    return t.vc > 0 && t.rows <= stage_passes(run.mirror, true) && lds(t, 1) <= kGroupLdsBytes;
+  };
+  TileShape ts = shape(kBrickZ);
+  if (ts.vc <= 0) return ts;
+  const bool few = bricks(ts) <= kResidentGroups;
+  if (few) {
+    for (int32_t np : {kMidBrickZ, kSmallBrickZ}) {
+      const TileShape t = shape(np);
+      if (staged(t) && (bricks(t) <= kCus || (ts.vc != kBpStageViews && np == kMidBrickZ))) ts = t;
+    }
+  }
+  if (!staged(ts) || (run.mirror && ts.vc != kBpStageViews && !few)) return ts;
+  ts.groups = bricks(ts) <= kCus ? kMaxGroups : 2 * bricks(ts) <= 3 * kCus ? 2 : 1;
+  while (ts.groups > 1 && (ts.groups > vb.nviews || lds(ts, ts.groups) > kGroupLdsBytes))
+    ts.groups /= 2;
+  ts.lds_bytes = lds(ts, ts.groups);
+  ts.wide = ts.wide || ts.groups > 1 || ts.np != kBrickZ || ts.vc != kBpStageViews ||
+            ts.rows != stage_passes(run.mirror, false);
   return ts;
 }
 
