@@ -161,6 +161,38 @@ __device__ __forceinline__ ColumnF32 column_f64(const GeoConst& gc, const ViewGe
   return c;
 }
 
+// Bounds for the adjoint's fixed-point sums. Most columns of the brick with floor(u) in {p - 1, p} for any p. Along a row
+// of the brick u(i + 1) - u(i) = ku (ai z - a ci)(j) / (z z'), whose numerator
+// depends on j alone and is affine in it, so the smallest spacing follows from
+// the brick's corners; an interval of two pixels then holds at most
+// ceil(2 / spacing) of a row's columns (2.002: rounding of u). Likewise along
+// j; the smaller total holds.
+__host__ __device__ inline int32_t columns_at_pixel(const GeoConst& gc, const ViewGeo& g, int32_t i_lo,
+                                                    int32_t i_hi, int32_t j_lo, int32_t j_hi) {
+  const int32_t ni = i_hi - i_lo + 1, nj = j_hi - j_lo + 1;
+  double zmax = 0.0;
+  for (int c = 0; c < 4; ++c)
+    zmax = fmax(zmax, fma(g.ci, (c & 1) ? i_hi : i_lo, fma(g.cj, (c & 2) ? j_hi : j_lo, g.c0)));
+  auto most = [&](double m, double n0, int32_t lo, int32_t hi, int32_t len) {
+    const double p = fma(m, lo, n0), q = fma(m, hi, n0);
+    const float spacing = p * q > 0.0 ? static_cast<float>(gc.ku * fmin(fabs(p), fabs(q)) / (zmax * zmax)) : 0.0f;
+    const float n = spacing > 0.0f ? ceilf(2.002f / spacing) : INFINITY;
+    return n < static_cast<float>(len) ? static_cast<int32_t>(n) : len;
+  };
+  const double m = g.ai * g.cj - g.ci * g.aj;
+  const int32_t along_i = most(m, g.ai * g.c0 - g.ci * g.a0, j_lo, j_hi, ni);
+  const int32_t along_j = most(-m, g.aj * g.c0 - g.cj * g.a0, i_lo, i_hi, nj);
+  const int32_t a = along_i * nj, b = along_j * ni;
+  return a < b ? a : b;
+}
+
+// Most slices of a column (of bz in the brick) with a tap on one row: those
+// with v in [r - 1, r + 1), one spare for the rounding of v. dvk: the
+// smallest dv/dk.
+__host__ __device__ inline float slots_at_row(float dvk, int32_t bz) {
+  return fminf(static_cast<float>(bz), floorf(2.0f / dvk) + 2.0f);
+}
+
 struct BrickCoords {
   int32_t i_lo, i_hi, j_lo, j_hi, i, j, t0, kb;
   float txf, tyf;
@@ -191,8 +223,10 @@ __device__ __forceinline__ void brick_index(const TileShape& ts, int32_t* bx, in
   *seg = static_cast<int32_t>(sg);
 }
 
+// across: groups of 16 threads run along y instead of x.
 __device__ __forceinline__ BrickCoords brick_coords(const GeoConst& gc, const SliceRun& run,
-                                                    const TileShape& ts, int32_t bz = kBrickZ) {
+                                                    const TileShape& ts, int32_t bz = kBrickZ,
+                                                    bool across = false) {
   int32_t bx, by, seg;
   brick_index(ts, &bx, &by, &seg);
   BrickCoords bc;
@@ -200,7 +234,9 @@ __device__ __forceinline__ BrickCoords brick_coords(const GeoConst& gc, const Sl
   bc.j_lo = by * kBrickY;
   bc.i_hi = min(bc.i_lo + kBrickX - 1, gc.nx - 1);
   bc.j_hi = min(bc.j_lo + kBrickY - 1, gc.ny - 1);
-  const int32_t tx0 = threadIdx.x % kBrickX, ty0 = threadIdx.x / kBrickX;
+  static_assert(kBrickX == kBrickY, "threads run along x or y");
+  const int32_t in = threadIdx.x % kBrickX, out = threadIdx.x / kBrickX;
+  const int32_t tx0 = across ? out : in, ty0 = across ? in : out;
   bc.owner = (bc.i_lo + tx0 <= bc.i_hi) && (bc.j_lo + ty0 <= bc.j_hi);
   bc.i = min(bc.i_lo + tx0, bc.i_hi);
   bc.j = min(bc.j_lo + ty0, bc.j_hi);

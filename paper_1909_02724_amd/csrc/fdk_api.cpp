@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <limits>
+#include <numeric>
 #include <string>
 #include <utility>
 #include <vector>
@@ -115,106 +116,61 @@ int32_t views_per_launch(int32_t nviews, int32_t cap) {
   return n > 0 ? (nviews + n - 1) / n : cap;
 }
 
-// Views per launch of the adjoint: up to kMaxViewsPerLaunch when every
-// launch's views then span at most kFpWideSpanRad of angle, else up to
-// kFpViewsPerLaunch.
-int32_t adjoint_views_per_launch(const double* angles, int32_t nviews) {
-  const int32_t wide = views_per_launch(nviews, fdk::kMaxViewsPerLaunch);
-  for (int32_t b = 0; b < nviews; b += wide) {
-    const int32_t n = std::min(wide, nviews - b);
-    const auto [lo, hi] = std::minmax_element(angles + b, angles + b + n);
-    if (*hi - *lo > fdk::kFpWideSpanRad) return views_per_launch(nviews, fdk::kFpViewsPerLaunch);
-  }
-  return wide;
+// Whether a view's rays run closer to x than to y in the lanes' plane: the
+// adjoint's LDS adds are served a group of 16 threads at a time, and threads
+// along a ray share a detector column, so groups run across the rays.
+bool rays_along_x(double beta) { return std::fabs(std::sin(beta)) > std::fabs(std::cos(beta)); }
+
+// Views of a call in the order its adjoint launches take them: by direction.
+std::vector<int32_t> adjoint_order(const double* angles, int32_t nviews) {
+  std::vector<int32_t> order(nviews);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_partition(order.begin(), order.end(),
+                        [&](int32_t s) { return !rays_along_x(angles[s]); });
+  return order;
 }
 
-// Adjoint slot rotation: the order in which each lane visits its 16 slots.
-// The tiled adjoint is bound by LDS bank conflicts among the 64 lanes of each
-// atomic add, and which rotation spreads them best depends on the view
-// angle (at 2048^3, 32-view batches took 201-339 ms with (tx + 4 ty) and
-// 201-248 ms with the best of four rotations). For large launches the host
-// scores the candidates with a model of the adds' addresses: per wave
-// instruction, the most lanes that fall in one of the 64 four-byte banks,
-// summed over sample bricks and views. A uniform shift of all addresses
-// leaves that count unchanged, so tile origins are not needed.
-constexpr int kRotCand[4][2] = {{1, 4}, {1, 5}, {3, 4}, {5, 4}};
-constexpr double kRotTuneMinWork = 2147483648.0;  // voxel-view updates per launch (2^31)
-constexpr double kRotSwitchRatio = 0.95;
-
-double rotation_cost(const fdk::GeoConst& gc, const fdk::ViewGeo& v, int32_t pitch, int32_t i_lo,
-                     int32_t j_lo, int32_t kb, int ra, int rb) {
-  double cost = 0.0;
-  int32_t base[64], rot[64];
-  double fvb[64], dvk[64];
-  for (int w = 0; w < 4; ++w) {
-    for (int l = 0; l < 64; ++l) {
-      const int tid = 64 * w + l, tx = tid % 16, ty = tid / 16;
-      const double i = std::min(i_lo + tx, gc.nx - 1), j = std::min(j_lo + ty, gc.ny - 1);
-      const double z = v.ci * i + v.cj * j + v.c0;
-      const double u = gc.cu + gc.ku * (v.ai * i + v.aj * j + v.a0) / z;
-      const double v0 = gc.cv + gc.kv * (kb - gc.cz) / z;
-      const double nvb = std::floor(v0);
-      base[l] = static_cast<int32_t>(std::floor(u)) * pitch + static_cast<int32_t>(nvb);
-      fvb[l] = v0 - nvb;
-      dvk[l] = gc.kv / z;
-      rot[l] = (ra * tx + rb * (ty & 3)) & 15;
+// Views order[0, n) as one launch of at most kMaxViewsPerLaunch: chunks of one
+// direction each, of at most `chunk` views. FDK_FP_ROT=a,b forces the slot
+// rotation of the kernels that take one slice at a time (a tuning aid).
+// Returns whether it does.
+bool adjoint_batch(const double* angles, const int32_t* order, int32_t n, int32_t chunk,
+                   fdk::FpBatch* fb) {
+  int a = 0, b = 0;
+  const char* env = std::getenv("FDK_FP_ROT");
+  const bool forced = env && std::sscanf(env, "%d,%d", &a, &b) == 2;
+  fb->rot_a = forced ? a : 8;
+  fb->rot_b = forced ? b : 4;
+  fb->vb.nviews = n;
+  fb->nchunks = 0;
+  for (int32_t s = 0; s < n;) {
+    const bool across = rays_along_x(angles[order[s]]);
+    int32_t run = 1;
+    while (s + run < n && rays_along_x(angles[order[s + run]]) == across) ++run;
+    const int32_t parts = (run + chunk - 1) / chunk;
+    for (int32_t p = 0; p < parts; ++p) {
+      fb->first[fb->nchunks] = static_cast<int16_t>(s + run * p / parts);
+      fb->across[fb->nchunks++] = across;
     }
-    for (int t = 0; t < 16; ++t) {
-      int32_t addr[64];
-      for (int l = 0; l < 64; ++l)
-        addr[l] = base[l] + static_cast<int32_t>(std::floor(fvb[l] + ((t + rot[l]) & 15) * dvk[l]));
-      const int32_t offs[4] = {0, pitch, 1, pitch + 1};  // the four taps of a splat
-      for (int32_t off : offs) {
-        int hist[64] = {0}, mx = 0;
-        for (int l = 0; l < 64; ++l) mx = std::max(mx, ++hist[(addr[l] + off) & 63]);
-        cost += mx;
-      }
-    }
+    s += run;
   }
-  return cost;
+  fb->first[fb->nchunks] = static_cast<int16_t>(n);
+  for (int32_t s = 0; s < n; ++s) {
+    fb->idx[s] = order[s];
+    fdk::set_view(&fb->vb, s, angles[order[s]]);
+  }
+  return forced;
 }
 
-// Picks ts->rot_a, rot_b for one adjoint launch (FDK_FP_ROT=a,b forces a
-// choice: a tuning aid).
-void choose_rotation(const fdk::GeoConst& gc, const fdk::SliceRun& r, const fdk::ViewBatch& vb,
-                     int32_t bz, fdk::TileShape* ts) {
-  if (const char* env = std::getenv("FDK_FP_ROT")) {
-    int a = 1, b = 4;
-    if (std::sscanf(env, "%d,%d", &a, &b) == 2) {
-      ts->rot_a = a;
-      ts->rot_b = b;
-    }
-    return;
-  }
-  if (ts->vc <= 0 || vb.nviews <= 0) return;  // the direct variant adds to global memory
-  if (static_cast<double>(gc.nx) * gc.ny * r.n * vb.nviews < kRotTuneMinWork) return;
-  static const double kFrac[5][3] = {
-      {0.1, 0.15, 0.0}, {0.5, 0.5, 0.5}, {0.8, 0.25, 0.95}, {0.95, 0.95, 0.06}, {0.3, 0.7, 0.3}};
-  const int32_t views[3] = {0, vb.nviews / 2, vb.nviews - 1};
-  double cost0 = 0.0, best = 0.0;
-  int bi = 0;
-  for (int c = 0; c < 4; ++c) {
-    double cost = 0.0;
-    for (int32_t s : views) {
-      for (const auto& f : kFrac) {
-        const int32_t bx = static_cast<int32_t>(f[0] * (ts->nbx - 1));
-        const int32_t by = static_cast<int32_t>(f[1] * (ts->nby - 1));
-        const int32_t seg = static_cast<int32_t>(f[2] * (ts->nseg - 1));
-        cost += rotation_cost(gc, fdk::view_geo(gc, vb.sn[s], vb.cs[s]), ts->tvp, bx * fdk::kBrickX, by * fdk::kBrickY,
-                              r.k_first + seg * bz, kRotCand[c][0], kRotCand[c][1]);
-      }
-    }
-    if (c == 0) cost0 = cost;
-    if (c == 0 || cost < best) {
-      best = cost;
-      bi = c;
-    }
-  }
-  // The model ranks close candidates unreliably: leave the default unless
-  // another is clearly better.
-  if (best > kRotSwitchRatio * cost0) bi = 0;
-  ts->rot_a = kRotCand[bi][0];
-  ts->rot_b = kRotCand[bi][1];
+// Views of a chunk: enough chunks for kFpGrid workgroups, but at least
+// kFpChunkViews views each, since every chunk reads the brick again and sets
+// it up. (128^3 from 90 views and 256^3 from 360: 1280 to 8192 workgroups
+// measure within 4 %, and 16 views a chunk cost 64^3 from 64 views 40 %.)
+constexpr int64_t kFpGrid = 4096;
+constexpr int32_t kFpChunkViews = 8;
+int32_t adjoint_chunk(int64_t bricks, int32_t nviews) {
+  const int64_t chunks = std::max<int64_t>(1, (kFpGrid + bricks - 1) / bricks);
+  return std::max<int32_t>(kFpChunkViews, static_cast<int32_t>((nviews + chunks - 1) / chunks));
 }
 
 struct Slab {
@@ -379,22 +335,25 @@ fdk_status fdk_forward_project(const fdk_geometry* g, int32_t view0, int32_t nvi
     if (int e = fdk::launch_fill_zero(q, vstride * nviews, stream))
       return fail(FDK_ERR_HIP, "zero fill failed: HIP error %d", e);
   }
-  fdk::ViewBatch vb;
-  const int32_t per = adjoint_views_per_launch(g->angles + view0, nviews);
+  fdk::FpBatch fb;
+  const double* const angles = g->angles + view0;
+  const std::vector<int32_t> order = adjoint_order(angles, nviews);
+  const int32_t per = views_per_launch(nviews, fdk::kMaxViewsPerLaunch);
   for (int32_t b = 0; b < nviews; b += per) {
-    vb.nviews = std::min(per, nviews - b);
-    for (int32_t s = 0; s < vb.nviews; ++s) fdk::set_view(&vb, s, g->angles[view0 + b + s]);
+    const int32_t n = std::min(per, nviews - b);
+    adjoint_batch(angles, order.data() + b, n, n, &fb);
     for (const fdk::SliceRun& r : sl.runs) {
       // Plain runs: 32-slice bricks and a single accumulation plane; their
       // flush has no prefetch budget to respect.
       fdk::TileShape ts =
-          r.mirror ? fdk::tile_shape(g, gc, r, vb, fdk::kBrickZ, fdk::kTileEntryBytes,
+          r.mirror ? fdk::tile_shape(g, gc, r, fb.vb, fdk::kBrickZ, fdk::kTileEntryBytes,
                                      fdk::kPrefetchSlots, direct)
-                   : fdk::tile_shape(g, gc, r, vb, fdk::kPlainBrickZ, fdk::kPlainEntryBytes,
+                   : fdk::tile_shape(g, gc, r, fb.vb, fdk::kPlainBrickZ, fdk::kPlainEntryBytes,
                                      std::numeric_limits<int32_t>::max(), direct);
-      choose_rotation(gc, r, vb, r.mirror ? fdk::kBrickZ : fdk::kPlainBrickZ, &ts);
-      if (int e = fdk::launch_forward_project(gc, r, vb, ts, vol, q + (size_t)b * vstride,
-                                              vstride, scale, fixed_sums, stream))
+      const int64_t bricks = static_cast<int64_t>(ts.nbx) * ts.nby * ts.nseg;
+      if (adjoint_batch(angles, order.data() + b, n, adjoint_chunk(bricks, n), &fb)) ts.span = 0;
+      if (int e = fdk::launch_forward_project(gc, r, fb, ts, vol, q, vstride, scale, fixed_sums,
+                                              stream))
         return fail(FDK_ERR_HIP, "forward-projection launch failed: HIP error %d", e);
     }
   }

@@ -13,15 +13,8 @@ namespace fdk {
 // back-projector writes) the volume once and sets up each brick once; the
 // views of a call are split evenly over the fewest launches. Measured at
 // 2048^3: the back-projector 6 % faster with 64 views a launch than with
-// 32, and 3 % faster again with 96. The adjoint takes 96 only when every
-// launch's views then span at most kFpWideSpanRad: one slot rotation serves
-// all views of a launch, and 96 views spread over 120 degrees cost it 11 %
-// at 2048^3, while launches over 68 and 90 degrees gained 3 % (512^3 from
-// 512 views, 256^3 from 360). Otherwise it takes at most 64 (2 % faster than
-// 32 at 2048^3, 10 % at 256^3 from 360 views).
+// 32, and 3 % faster again with 96.
 constexpr int kMaxViewsPerLaunch = 96;
-constexpr int kFpViewsPerLaunch = 64;
-constexpr double kFpWideSpanRad = 1.75;  // about 100 degrees
 
 // Per-view geometry in the reduced-cost form of Alg. 4, evaluated in FP64
 // from the sine and cosine of the view angle (Eq. 2 expanded; view_geo, on
@@ -73,6 +66,19 @@ struct ViewBatch {
   int32_t nviews;
 };
 
+// Views of an adjoint launch: view s is projection idx[s] of the call. Chunk c,
+// the blockIdx.y of a workgroup, takes views [first[c], first[c + 1]), whose
+// rays run closer to y than to x if across[c] is 0, else closer to x: groups
+// of 16 threads then run along x or y, across the rays. rot_a, rot_b: see
+// slot_rotation (fp.hip).
+constexpr int kMaxChunks = 32;
+struct FpBatch {
+  ViewBatch vb;
+  int32_t idx[kMaxViewsPerLaunch];
+  int32_t nchunks, rot_a, rot_b;
+  int16_t first[kMaxChunks + 1], across[kMaxChunks];
+};
+
 // Bricked back-projection: a workgroup of 256 threads owns a brick of
 // kBrickX x kBrickY columns and kBrickZ consecutive slices of a slice run
 // (plus their mirrors for a mirrored run). In the tiled variant it stages
@@ -112,9 +118,6 @@ struct TileShape {
   int32_t groups;        // back-projector: 256-thread groups per workgroup (0: the general kernel)
   int32_t lds_bytes;     // back-projector: dynamic LDS of a workgroup
   int32_t nbx, nby, nseg;  // bricks along x, y and z-segments of the run
-  // Adjoint: lane (tx, ty) visits its slots from (rot_a tx + rot_b (ty mod 4))
-  // mod 16 on, which spreads the lanes' LDS adds over the banks.
-  int32_t rot_a, rot_b;
 };
 
 // Kernel choice for a run and view batch: tiled unless the footprint tile
@@ -159,7 +162,7 @@ int launch_backproject(const GeoConst& gc, const SliceRun& run, const ViewBatch&
                        const TileShape& ts, const void* q, fdk_dtype q_dtype,
                        int64_t view_stride, float* vol, float scale, int accumulate,
                        void* stream);
-int launch_forward_project(const GeoConst& gc, const SliceRun& run, const ViewBatch& vb,
+int launch_forward_project(const GeoConst& gc, const SliceRun& run, const FpBatch& fb,
                            const TileShape& ts, const float* vol, float* q, int64_t view_stride,
                            float scale, bool fixed_sums, void* stream);
 int launch_fill_zero(float* p, int64_t n, void* stream);

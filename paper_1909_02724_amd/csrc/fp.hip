@@ -37,14 +37,22 @@ __device__ __forceinline__ void splat(float* __restrict__ qs, int32_t nu, int32_
   }
 }
 
-// Slot order of a lane in the adjoint. Lanes of a wave that share a detector
-// column (along the rays) would otherwise add to the same LDS or global
-// address in the same instruction, which serialises; rotating each lane's
-// walk over its 16 slots by (tx + 4 ty) mod 16 puts such lanes on
-// different rows.
-__device__ __forceinline__ uint32_t slot_rotation(const TileShape& ts) {
-  const uint32_t tx = threadIdx.x % kBrickX, ty = (threadIdx.x / kBrickX) & 3u;
-  return (static_cast<uint32_t>(ts.rot_a) * tx + static_cast<uint32_t>(ts.rot_b) * ty) &
+// Slot order of a lane in the adjoint. The LDS serves 64-bit adds 16 lanes and
+// 32-bit ones 32 lanes at a time; lanes of such a group that add to one bank
+// take turns, and to one address twice over (measured: m lanes on one
+// address take 2m - 1 turns). Lanes along a ray share a detector column, so
+// groups of 16 run across the rays (FpBatch::across), and each lane starts its
+// 16 slots at another one, so that lanes that share a column all the same are
+// on different rows: at (a in + b (out mod 4)) mod 16, with `in` the lane's
+// place in its group and `out` the group's.
+// The row walk (HALVES) knows two starts only, slot 0 and slot 8, by the
+// parity of in + out. In a model of the addresses over all angles, at 0.75 to
+// 1.33 pixels a voxel, its 64-bit adds then take 8.3 clocks a wave
+// instruction (6.2 without a meeting; 40 to 100 with groups along the rays).
+__device__ __forceinline__ uint32_t slot_rotation(const FpBatch& fb, bool halves) {
+  const uint32_t in = threadIdx.x % kBrickX, out = threadIdx.x / kBrickX;
+  if (halves) return ((in + out) & 1u) * (kBrickZ / 2);
+  return (static_cast<uint32_t>(fb.rot_a) * in + static_cast<uint32_t>(fb.rot_b) * (out & 3u)) &
          (kBrickZ - 1);
 }
 
@@ -57,18 +65,17 @@ __device__ __forceinline__ void load_voxels(const GeoConst& gc, const SliceRun& 
                                             float scale, uint32_t rot, float* x, float* xm) {
   const int64_t slice = static_cast<int64_t>(gc.nx) * gc.ny;
   const int64_t col = static_cast<int64_t>(bc.j) * gc.nx + bc.i;
+  // Every load is issued, at a slice clamped to the run, and what is not the
+  // thread's is dropped: no branch, so all loads are in flight together.
+  const int32_t top = run.n - 1 - bc.t0;
 #pragma unroll
   for (int t = 0; t < kBrickZ; ++t) {
     const int32_t sl = static_cast<int32_t>((t + rot) & (kBrickZ - 1));
-    const bool in = bc.owner && (bc.t0 + sl < run.n);
-    x[t] = in ? scale * vol[static_cast<int64_t>(run.loc_lo + bc.t0 + sl) * slice + col] : 0.0f;
-    if (MIRROR) {
-      xm[t] = in ? scale * vol[static_cast<int64_t>(run.loc_hi - bc.t0 - sl) * slice + col] : 0.0f;
-    } else {
-      const bool in2 = bc.owner && (bc.t0 + kBrickZ + sl < run.n);
-      xm[t] = in2 ? scale * vol[static_cast<int64_t>(run.loc_lo + bc.t0 + kBrickZ + sl) * slice + col]
-                  : 0.0f;
-    }
+    const float v = vol[static_cast<int64_t>(run.loc_lo + bc.t0 + min(sl, top)) * slice + col];
+    x[t] = bc.owner && sl <= top ? scale * v : 0.0f;
+    const int32_t up = MIRROR ? min(sl, top) : min(kBrickZ + sl, top);
+    const float m = vol[static_cast<int64_t>(MIRROR ? run.loc_hi - bc.t0 - up : run.loc_lo + bc.t0 + up) * slice + col];
+    xm[t] = bc.owner && (MIRROR ? sl : kBrickZ + sl) <= top ? scale * m : 0.0f;
   }
 }
 
@@ -104,8 +111,13 @@ __device__ __forceinline__ void load_voxels(const GeoConst& gc, const SliceRun& 
 //    floor(2 / (dv/dk)) + 2 of them (one spare for the rounding of v), and
 //    never more than the brick's slice count;
 //  - each contribution is at most M = max over columns of max|x| * W.
-// A histogram over floor(u) of the per-column slot bounds gives K, the most
-// contributions any pixel can receive; S = 2^(31 - e) with 1.01 K M < 2^e
+// K, the most contributions any pixel can receive, is bounded per brick and
+// view from its corners (columns_at_pixel times slots_at_row, brick.h; on
+// average 1.2 times the most any pixel does receive. A histogram of the
+// columns' pixels gave the exact maximum, at two more barriers and column
+// setups a stage and LDS atomics that all lanes send to a few addresses:
+// 16.3 ms, of which 14.0 remained without it at 512^3 from 128 views).
+// S = 2^(31 - e) with 1.01 K M < 2^e
 // keeps every partial sum, rounding included, inside int32. S is a power of
 // two, so the scaling is exact and cannot overflow however small or large
 // the values. A pixel's quantisation error is at most half a unit,
@@ -113,8 +125,6 @@ __device__ __forceinline__ void load_voxels(const GeoConst& gc, const SliceRun& 
 // units, whose FP32 value is coarser than that anyway): relative to the
 // brick's largest splat, not to the pixel's own sum, which is why
 // wide-range bricks take 64 bits or FP32.
-constexpr int32_t kHistStride = kThreads;  // tile columns tu + 1 <= 256
-constexpr int64_t kFpSplitTarget = 4096;    // workgroups below which views are split
 constexpr int kFpWideRangeLog2 = 13;        // "small" voxels: below 2^-13 of the brick's max
 constexpr int kFpWideRangePct = 1;          // wide-range path above 1 % small voxels
 constexpr int kFp64RangeLog2 = 40;          // 64-bit fixed point up to this magnitude range
@@ -159,35 +169,99 @@ __device__ __forceinline__ void add_fixed64(uint64_t* p, float x) {
             static_cast<unsigned long long>(__float2ll_rn(x)));
 }
 
-template <bool MIRROR>
-__device__ __forceinline__ void fp_tiled_body(GeoConst gc, SliceRun run, ViewBatch vb,
-                                              TileShape ts, const float* __restrict__ vol,
+// Largest of x over the wave, in lane 63: DPP moves within rows of 16 lanes,
+// then row broadcasts.
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+#define FDK_DPP_MAX(ctrl, rows)                                                              \
+  x = max(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(                              \
+                 0, static_cast<int>(x), ctrl, rows, 0xF, false)))
+  FDK_DPP_MAX(0x111, 0xF);  // row_shr:1, 2, 4, 8
+  FDK_DPP_MAX(0x112, 0xF);
+  FDK_DPP_MAX(0x114, 0xF);
+  FDK_DPP_MAX(0x118, 0xF);
+  FDK_DPP_MAX(0x142, 0xA);  // row_bcast:15
+  FDK_DPP_MAX(0x143, 0xC);  // row_bcast:31
+#undef FDK_DPP_MAX
+  return x;
+}
+
+// Row sums of kWalk slices of a column, the back-projector's row walk
+// transposed. Where v drifts by less than a pixel against rows one apart over
+// the slices, slice k has its taps in rows k, k + 1, k + 2 of the block's
+// kWalk + 2 (weights 1 - a, a - b, b with a, b the clamped offsets), so each
+// row is summed in a register and added to the tile once per pixel column: 40
+// LDS adds per 16 slices (or pairs) instead of 64, at constant offsets, and
+// 435 VALU instructions a wave and view instead of 600. The kernel stays
+// bound by LDS adds (62 % of the cycles, 43 % of those for lanes that meet)
+// beside VALU issue (48 % at the full rate). 512^3 from 128 views: 15.5 -> 9.4
+// ms with the bounds, thread groups and tile pitch above; 215 x 190 x 171 at
+// 1.2 pixels a voxel, which takes one slice at a time: 1.17 -> 0.69 ms.
+//   emit(row, sum, sum of mirrors)
+constexpr int kWalk = kBrickZ / 2;
+template <bool MIRROR, class Emit>
+__device__ __forceinline__ void walk_rows(float o, float eps, const float* x, const float* xm,
+                                          Emit emit) {
+  float c0 = 0.0f, c1 = 0.0f, m0 = 0.0f, m1 = 0.0f;  // pending sums of the next two rows
+  const float o1 = o - 1.0f;
+#pragma unroll
+  for (int t = 0; t < kWalk; ++t) {
+    const float a = __builtin_amdgcn_fmed3f(fmaf(static_cast<float>(t), eps, o), 0.0f, 1.0f);
+    const float b = __builtin_amdgcn_fmed3f(fmaf(static_cast<float>(t), eps, o1), 0.0f, 1.0f);
+    const float w0 = 1.0f - a, w1 = a - b;
+    float msum = 0.0f;
+    if constexpr (MIRROR) {
+      msum = fmaf(xm[t], w0, m0);
+      m0 = fmaf(xm[t], w1, m1);
+      m1 = xm[t] * b;
+    }
+    emit(t, fmaf(x[t], w0, c0), msum);
+    c0 = fmaf(x[t], w1, c1);
+    c1 = x[t] * b;
+    asm volatile("" ::: "memory");  // one step's values at a time in registers
+  }
+  emit(kWalk, c0, m0);
+  emit(kWalk + 1, c1, m1);
+}
+
+template <bool MIRROR, bool WALK>
+__device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun& run,
+                                              const FpBatch& fb, const TileShape& ts, const float* __restrict__ vol,
                                               float* __restrict__ q, int64_t vstride,
                                               float scale, int fixed_sums) {
   extern __shared__ __attribute__((aligned(16))) int atile[];
   __shared__ BrickView bvs[kMaxViewsPerLaunch];
-  __shared__ uint32_t hist[kMaxStageViews * kHistStride];
-  __shared__ uint32_t kcount[kMaxStageViews], mbits[kMaxStageViews];
+  __shared__ float kw[kMaxViewsPerLaunch];  // 1.01 K times the largest W of the brick's columns
   __shared__ uint32_t amax_bits, amin_bits, n_nonzero, n_small, nonfinite;
   const int32_t tid = threadIdx.x;
   constexpr int BZ = MIRROR ? kBrickZ : kPlainBrickZ;  // slices per brick
-  // blockIdx.y picks this workgroup's share of the launch's views: small
-  // volumes split the views over several workgroups per brick (the
-  // projections take their sums through atomics either way), so the grid
-  // fills the chip more than once over.
-  const int32_t per = (vb.nviews + static_cast<int32_t>(gridDim.y) - 1) / static_cast<int32_t>(gridDim.y);
-  const int32_t v_lo = static_cast<int32_t>(blockIdx.y) * per;
-  const int32_t v_hi = min(vb.nviews, v_lo + per);
-  if (v_lo >= v_hi) return;  // uniform, before any barrier
-  const BrickCoords bc = brick_coords(gc, run, ts, BZ);
+  // blockIdx.y picks this workgroup's chunk of the launch's views.
+  const ViewBatch& vb = fb.vb;
+  const int32_t v_lo = fb.first[blockIdx.y], v_hi = fb.first[blockIdx.y + 1];
+  const BrickCoords bc = brick_coords(gc, run, ts, BZ, fb.across[blockIdx.y] != 0);
   if (tid == 0) {
     amax_bits = n_nonzero = n_small = nonfinite = 0u;
     amin_bits = __float_as_uint(INFINITY);
   }
-  if (tid >= v_lo && tid < v_hi)
-    bvs[tid] = brick_setup(gc, view_geo(gc, vb.sn[tid], vb.cs[tid]), bc.i_lo, bc.i_hi, bc.j_lo, bc.j_hi, bc.kb, 0, 0, BZ,
-                           MIRROR);
-  const uint32_t rot = slot_rotation(ts);
+  const float kvf = static_cast<float>(gc.kv);
+  if (tid >= v_lo && tid < v_hi) {
+    BrickView b = brick_setup(gc, view_geo(gc, vb.sn[tid], vb.cs[tid]), bc.i_lo, bc.i_hi, bc.j_lo,
+                              bc.j_hi, bc.kb, 0, 0, BZ, MIRROR);
+    // z is affine in (i, j): W, dv/dk and the drift of v are extremal at corners.
+    float w = 0.0f, drift = 0.0f, dvk = INFINITY;
+    for (int c = 0; c < 4; ++c) {
+      const ColumnF32 col = column_f32(b, (c & 1) ? static_cast<float>(bc.i_hi - bc.i_lo) : 0.0f,
+                                       (c & 2) ? static_cast<float>(bc.j_hi - bc.j_lo) : 0.0f, kvf);
+      w = fmaxf(w, col.w);
+      drift = fmaxf(drift, fabsf(col.eps));
+      dvk = fminf(dvk, col.dvk);
+    }
+    kw[tid] = 1.01f * slots_at_row(dvk, BZ) *
+              static_cast<float>(columns_at_pixel(gc, view_geo(gc, vb.sn[tid], vb.cs[tid]), bc.i_lo,
+                                                  bc.i_hi, bc.j_lo, bc.j_hi)) * w;
+    b.inside = static_cast<float>(kWalk - 1) * drift <= static_cast<float>(kSpanDrift);  // the walk holds
+    bvs[tid] = b;
+  }
+  const uint32_t rot = slot_rotation(fb, WALK);
   float x[kBrickZ], xm[kBrickZ];
   load_voxels<MIRROR>(gc, run, bc, vol, scale, rot, x, xm);
   // Brick statistics: largest and smallest non-zero magnitudes, non-finite
@@ -203,8 +277,14 @@ __device__ __forceinline__ void fp_tiled_body(GeoConst gc, SliceRun run, ViewBat
     bad = bad || ((x[t] - x[t]) != 0.0f) || ((xm[t] - xm[t]) != 0.0f);
   }
   __syncthreads();
-  atomicMax(&amax_bits, __float_as_uint(amax));  // non-negative floats order as integers
-  atomicMin(&amin_bits, __float_as_uint(amin));
+  // One LDS atomic a wave (64 lanes on one address serialise). Non-negative
+  // floats order as integers; the smallest is the largest complement.
+  const bool last = (tid & (kWaveLanes - 1)) == kWaveLanes - 1;
+  const uint32_t hi = wave_max(__float_as_uint(amax)), lo = ~wave_max(~__float_as_uint(amin));
+  if (last) {
+    atomicMax(&amax_bits, hi);
+    atomicMin(&amin_bits, lo);
+  }
   if (bad) nonfinite = 1u;
   __syncthreads();
   {
@@ -215,8 +295,17 @@ __device__ __forceinline__ void fp_tiled_body(GeoConst gc, SliceRun run, ViewBat
       nz += (x[t] != 0.0f) + (xm[t] != 0.0f);
       ns += (x[t] != 0.0f && fabsf(x[t]) < small) + (xm[t] != 0.0f && fabsf(xm[t]) < small);
     }
-    if (nz) atomicAdd(&n_nonzero, nz);
-    if (ns) atomicAdd(&n_small, ns);
+    // Sums over the wave bit by bit (a thread counts at most 32 voxels).
+    uint32_t wnz = 0, wns = 0;
+#pragma unroll
+    for (int m = 0; m < 6; ++m) {
+      wnz += static_cast<uint32_t>(__popcll(__ballot((nz >> m) & 1u))) << m;
+      wns += static_cast<uint32_t>(__popcll(__ballot((ns >> m) & 1u))) << m;
+    }
+    if (last) {
+      atomicAdd(&n_nonzero, wnz);
+      atomicAdd(&n_small, wns);
+    }
   }
   __syncthreads();
   if (amax_bits == 0u && nonfinite == 0u) return;  // an all-zero brick adds nothing (uniform)
@@ -234,11 +323,26 @@ __device__ __forceinline__ void fp_tiled_body(GeoConst gc, SliceRun run, ViewBat
   const bool fp32_path = nonfinite != 0u || (wide_range && !fixed64);
   const int32_t vstep = fixed64 ? ts.vc / 2 : ts.vc;
 
-  const float kvf = static_cast<float>(gc.kv);
+  // Fixed point: the voxels are scaled by a power of two to magnitudes below
+  // 1, so that neither their sums nor the scale of the sums leave FP32's
+  // normal range whatever the volume's units are (the flush undoes it).
+  int ex_max = 0;
+  const float amax_1 = frexpf(__uint_as_float(amax_bits), &ex_max);
+  if (!fp32_path) {
+#pragma unroll
+    for (int t = 0; t < kBrickZ; ++t) {
+      x[t] = ldexpf(x[t], -ex_max);
+      xm[t] = ldexpf(xm[t], -ex_max);
+    }
+  }
   const int32_t tuf = ts.tu + 1, tv = ts.tv, tvp = ts.tvp;
   const int32_t slot = tuf * tvp;
   const int32_t rstep = kThreads / tuf;
   const int32_t sr = tid / tuf, sc = tid - sr * tuf;
+  // Tiles start at zero; the flush leaves them so for the next stage.
+  for (int32_t e = tid; e < (MIRROR ? 2 : 1) * ts.vc * slot; e += kThreads) atile[e] = 0;
+  __syncthreads();
+  int* const mtile = atile + ts.vc * slot;
   for (int32_t s0 = v_lo; s0 < v_hi; s0 += vstep) {
     const int32_t nvc = min(vstep, v_hi - s0);
     // Main rows in planes [0, vc) and mirror rows in planes [vc, 2 vc), one
@@ -247,40 +351,12 @@ __device__ __forceinline__ void fp_tiled_body(GeoConst gc, SliceRun run, ViewBat
     // (The 32-bit fixed-point path of mirrored runs uses the same bytes as
     // 64-bit (main, mirror) words instead, the 64-bit one as 16-byte
     // (main, mirror) entries, and that of plain runs as 64-bit words.)
-    int* const mtile = atile + ts.vc * slot;
-    for (int32_t e = tid; e < (MIRROR ? 2 : 1) * ts.vc * slot; e += kThreads) atile[e] = 0;
-    if (!fp32_path) {
-      for (int32_t e = tid; e < nvc * kHistStride; e += kThreads) hist[e] = 0u;
-      if (tid < nvc) kcount[tid] = mbits[tid] = 0u;
-    }
-    __syncthreads();
-    if (!fp32_path) {
-      // Bounds: histogram of the columns' slot bounds over floor(u), and
-      // the largest contribution.
-      if (bc.owner) {
-        for (int32_t sl = 0; sl < nvc; ++sl) {
-          const ColumnF32 c = column_f32(bvs[s0 + sl], bc.txf, bc.tyf, kvf);
-          const uint32_t nu = min(c.nu, static_cast<uint32_t>(ts.tu - 1));
-          const float ks = fminf(static_cast<float>(BZ), floorf(2.0f / c.dvk) + 2.0f);
-          atomicAdd(&hist[sl * kHistStride + nu], static_cast<uint32_t>(ks));
-          atomicMax(&mbits[sl], __float_as_uint(amax * c.w));
-        }
-      }
-      __syncthreads();
-      if (tid < tuf) {
-        for (int32_t sl = 0; sl < nvc; ++sl) {
-          const uint32_t* h = hist + sl * kHistStride;
-          atomicMax(&kcount[sl], (tid < ts.tu ? h[tid] : 0u) + (tid > 0 ? h[tid - 1] : 0u));
-        }
-      }
-      __syncthreads();
-    }
     if (bc.owner) {
       for (int32_t sl = 0; sl < nvc; ++sl) {
         const ColumnF32 c = column_f32(bvs[s0 + sl], bc.txf, bc.tyf, kvf);
         const uint32_t nu = min(c.nu, static_cast<uint32_t>(ts.tu - 1));
         if (!fp32_path) {
-          const float km = 1.01f * static_cast<float>(kcount[sl]) * __uint_as_float(mbits[sl]);
+          const float km = kw[s0 + sl] * amax_1;
           if (!(km > 0.0f)) continue;  // nothing reaches this view (uniform)
           int e;
           frexpf(km, &e);
@@ -338,6 +414,39 @@ __device__ __forceinline__ void fp_tiled_body(GeoConst gc, SliceRun run, ViewBat
             continue;
           }
           const float ws = ldexpf(c.w, 31 - e);  // W S, S = 2^(31 - e)
+          if (WALK && __builtin_amdgcn_readfirstlane(bvs[s0 + sl].inside)) {
+            // Blocks of kWalk slices, the lane's first one first; weights of
+            // the pixel columns u and u + 1 with the scale folded in.
+            const float v0 = ws * du0, v1 = ws * c.du;
+            const float down = fminf(static_cast<float>(kWalk - 1) * c.eps, 0.0f);
+#pragma unroll
+            for (int p = 0; p < BZ / kWalk; ++p) {
+              // First slice of block p of the column; its values are at kWalk (p mod 2).
+              const int32_t k0 = (p & ~1) * kWalk + ((p & 1) ? kWalk - static_cast<int32_t>(rot)
+                                                             : static_cast<int32_t>(rot));
+              const float* const xs = (p < 2 ? x : xm) + (p & 1) * kWalk;
+              const float o = fmaf(static_cast<float>(k0), c.eps, c.vl);
+              const float n = floorf(o + down);
+              const int32_t at = sl * slot + nu * tvp + k0 + static_cast<int32_t>(n);
+              if constexpr (MIRROR) {
+                uint64_t* const w = reinterpret_cast<uint64_t*>(atile) + at;
+                uint64_t* const w1 = w + tvp;
+                walk_rows<true>(o - n, c.eps, xs, xm + (p & 1) * kWalk,
+                                [&](int r, float sum, float msum) {
+                                  add_pair(w + r, sum * v0, msum * v0);
+                                  add_pair(w1 + r, sum * v1, msum * v1);
+                                });
+              } else {
+                int* const w = atile + at;
+                int* const w1 = w + tvp;
+                walk_rows<false>(o - n, c.eps, xs, nullptr, [&](int r, float sum, float) {
+                  atomicAdd(w + r, fixed_round(sum * v0));
+                  atomicAdd(w1 + r, fixed_round(sum * v1));
+                });
+              }
+            }
+            continue;
+          }
           if constexpr (MIRROR) {
             // (main, mirror) pairs of 32-bit sums in 64-bit words.
             uint64_t* const base = reinterpret_cast<uint64_t*>(atile) + sl * slot + nu * tvp + c.nvb;
@@ -413,44 +522,52 @@ __device__ __forceinline__ void fp_tiled_body(GeoConst gc, SliceRun run, ViewBat
       for (int32_t sl = 0; sl < nvc; ++sl) {
         const int32_t s = s0 + sl;
         const int32_t gu = bvs[s].org_u + sc;
-        if (static_cast<uint32_t>(gu) >= static_cast<uint32_t>(gc.nu)) continue;
-        // Value of one fixed-point unit: 2^(e - 31), or 2^(e - 63) for the
-        // 64-bit path (unused on the FP32 path).
-        float inv_s = 0.0f;
-        double inv_s64 = 0.0;
+        const bool on = static_cast<uint32_t>(gu) < static_cast<uint32_t>(gc.nu);
+        // One fixed-point unit is 2^unit (unused on the FP32 path).
+        int unit = 0;
         if (!fp32_path) {
           int e;
-          frexpf(1.01f * static_cast<float>(kcount[sl]) * __uint_as_float(mbits[sl]), &e);
-          inv_s = ldexpf(1.0f, e - 31);
-          inv_s64 = ldexp(1.0, e - 63);
+          frexpf(kw[s] * amax_1, &e);
+          unit = e + ex_max - (fixed64 ? 63 : 31);
         }
-        float* qs = q + s * vstride + gu;
+        float* qs = q + fb.idx[s] * vstride + gu;
         for (int32_t r = sr; r < tv; r += rstep) {
           const int32_t at = sl * slot + sc * tvp + r;
           float ex, ey = 0.0f;
           if (fp32_path) {
             ex = __int_as_float(atile[at]);
-            if (MIRROR) ey = __int_as_float(mtile[at]);
+            atile[at] = 0;
+            if (MIRROR) {
+              ey = __int_as_float(mtile[at]);
+              mtile[at] = 0;
+            }
           } else if (fixed64) {
-            const int64_t* const w = reinterpret_cast<const int64_t*>(atile);
-            ex = static_cast<float>(static_cast<double>(w[MIRROR ? 2 * at : at]) * inv_s64);
-            if (MIRROR) ey = static_cast<float>(static_cast<double>(w[2 * at + 1]) * inv_s64);
+            int64_t* const w = reinterpret_cast<int64_t*>(atile) + (MIRROR ? 2 * at : at);
+            ex = static_cast<float>(ldexp(static_cast<double>(w[0]), unit));
+            w[0] = 0;
+            if (MIRROR) {
+              ey = static_cast<float>(ldexp(static_cast<double>(w[1]), unit));
+              w[1] = 0;
+            }
           } else if (MIRROR) {
             // Word = (mirror sum) 2^32 + (main sum), both int32.
-            const uint64_t w = reinterpret_cast<const uint64_t*>(atile)[at];
+            uint64_t* const p = reinterpret_cast<uint64_t*>(atile) + at;
+            const uint64_t w = *p;
+            *p = 0;
             const int32_t lo = static_cast<int32_t>(static_cast<uint32_t>(w));
             const int32_t hi = static_cast<int32_t>((w - static_cast<uint64_t>(static_cast<int64_t>(lo))) >> 32);
-            ex = static_cast<float>(lo) * inv_s;
-            ey = static_cast<float>(hi) * inv_s;
+            ex = ldexpf(static_cast<float>(lo), unit);
+            ey = ldexpf(static_cast<float>(hi), unit);
           } else {
-            ex = static_cast<float>(atile[at]) * inv_s;
+            ex = ldexpf(static_cast<float>(atile[at]), unit);
+            atile[at] = 0;
           }
           const int32_t gr = bvs[s].org_v + r;
-          if (ex != 0.0f && static_cast<uint32_t>(gr) < static_cast<uint32_t>(gc.nv))
+          if (on && ex != 0.0f && static_cast<uint32_t>(gr) < static_cast<uint32_t>(gc.nv))
             unsafeAtomicAdd(qs + static_cast<int64_t>(gr) * gc.nu, ex);
           if (MIRROR) {
             const int32_t gm = gc.mirror_g - gr;
-            if (ey != 0.0f && static_cast<uint32_t>(gm) < static_cast<uint32_t>(gc.nv))
+            if (on && ey != 0.0f && static_cast<uint32_t>(gm) < static_cast<uint32_t>(gc.nv))
               unsafeAtomicAdd(qs + static_cast<int64_t>(gm) * gc.nu, ey);
           }
         }
@@ -460,52 +577,50 @@ __device__ __forceinline__ void fp_tiled_body(GeoConst gc, SliceRun run, ViewBat
   }
 }
 
-template <bool MIRROR>
-__global__ void fp_tiled_kernel(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,
-                                const float* __restrict__ vol, float* __restrict__ q,
-                                int64_t vstride, float scale, int fixed_sums);
-
-// Mirrored runs: six 256-thread workgroups per CU (80 VGPRs). The 64-bit
-// paths' code otherwise lifts the register count past it, and five
-// workgroups cost 11 % at 2048^3. (Held to 80 registers, the plain variant
-// spills inside its splat loops, so it keeps its count.)
-template <>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6)))
-void fp_tiled_kernel<true>(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,
-                           const float* __restrict__ vol, float* __restrict__ q, int64_t vstride,
-                           float scale, int fixed_sums) {
-  fp_tiled_body<true>(gc, run, vb, ts, vol, q, vstride, scale, fixed_sums);
+// Mirrored runs that take one slice at a time: six 256-thread workgroups per CU
+// (80 VGPRs). The 64-bit paths' code otherwise lifts the register count past
+// it, and five workgroups cost 11 % at 2048^3. Those that walk: five (96
+// VGPRs; six spill, 1 % faster at 512^3 and 5 to 24 % slower at 64^3 to 256^3).
+// (Held to 80 registers, the plain variant spills inside its splat loops, so
+// it keeps its count.)
+template <bool WALK>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WALK ? 5 : 6)))
+void fp_mirror_kernel(GeoConst gc, SliceRun run, FpBatch fb, TileShape ts,
+                      const float* __restrict__ vol, float* __restrict__ q, int64_t vstride,
+                      float scale, int fixed_sums) {
+  fp_tiled_body<true, WALK>(gc, run, fb, ts, vol, q, vstride, scale, fixed_sums);
 }
 
-template <>
+template <bool WALK>
 __global__ __launch_bounds__(kThreads)
-void fp_tiled_kernel<false>(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,
-                            const float* __restrict__ vol, float* __restrict__ q, int64_t vstride,
-                            float scale, int fixed_sums) {
-  fp_tiled_body<false>(gc, run, vb, ts, vol, q, vstride, scale, fixed_sums);
+void fp_plain_kernel(GeoConst gc, SliceRun run, FpBatch fb, TileShape ts,
+                     const float* __restrict__ vol, float* __restrict__ q, int64_t vstride,
+                     float scale, int fixed_sums) {
+  fp_tiled_body<false, WALK>(gc, run, fb, ts, vol, q, vstride, scale, fixed_sums);
 }
 
 template <bool MIRROR>
 __global__ __launch_bounds__(kThreads) void fp_direct_kernel(GeoConst gc, SliceRun run,
-                                                             ViewBatch vb, TileShape ts,
+                                                             FpBatch fb, TileShape ts,
                                                              const float* __restrict__ vol,
                                                              float* __restrict__ q,
                                                              int64_t vstride, float scale) {
   __shared__ BrickView bvs[kMaxViewsPerLaunch];
+  const ViewBatch& vb = fb.vb;
   const int32_t tid = threadIdx.x;
   constexpr int BZ = MIRROR ? kBrickZ : kPlainBrickZ;  // slices per brick
   const BrickCoords bc = brick_coords(gc, run, ts, BZ);
   if (tid < vb.nviews)
     bvs[tid] = brick_setup(gc, view_geo(gc, vb.sn[tid], vb.cs[tid]), bc.i_lo, bc.i_hi, bc.j_lo, bc.j_hi, bc.kb, 0, 0, BZ,
                            MIRROR);
-  const uint32_t rot = slot_rotation(ts);
+  const uint32_t rot = slot_rotation(fb, false);
   float x[kBrickZ], xm[kBrickZ];
   load_voxels<MIRROR>(gc, run, bc, vol, scale, rot, x, xm);
   __syncthreads();
   if (!bc.owner) return;
   for (int32_t s = 0; s < vb.nviews; ++s) {
     const ColumnF32 c = column_f64(gc, view_geo(gc, vb.sn[s], vb.cs[s]), bvs[s], bc.i, bc.j, bc.kb);
-    float* qs = q + s * vstride;
+    float* qs = q + fb.idx[s] * vstride;
     const int32_t a = bvs[s].org_u + static_cast<int32_t>(c.nu);
     const int32_t nb = bvs[s].org_v + static_cast<int32_t>(c.nvb);
 #pragma unroll
@@ -539,43 +654,40 @@ __global__ void fill_zero_kernel(float* __restrict__ p, int64_t n) {
 
 }  // namespace
 
-int launch_forward_project(const GeoConst& gc, const SliceRun& run, const ViewBatch& vb,
+int launch_forward_project(const GeoConst& gc, const SliceRun& run, const FpBatch& fb,
                            const TileShape& ts, const float* vol, float* q, int64_t vstride,
                            float scale, bool fixed_sums, void* stream) {
   const uint64_t nwg = static_cast<uint64_t>(ts.nbx) * ts.nby * ts.nseg;
   const dim3 block(kThreads);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (ts.vc > 0) {
-    // Views split over workgroups when the bricks alone give fewer than
-    // kFpSplitTarget workgroups.
-    int64_t vsplit = 1;
-    if (nwg < static_cast<uint64_t>(kFpSplitTarget))
-      vsplit = (kFpSplitTarget + static_cast<int64_t>(nwg) - 1) / static_cast<int64_t>(nwg);
-    vsplit = std::max<int64_t>(1, std::min<int64_t>(vsplit, vb.nviews));
-    const dim3 grid(static_cast<uint32_t>(nwg), static_cast<uint32_t>(vsplit));
+    const dim3 grid(static_cast<uint32_t>(nwg), static_cast<uint32_t>(fb.nchunks));
     // Adjoint tile: one more column than the back-projection tile, one
     // 32-bit word per pixel and plane (main, plus mirror for mirrored runs).
     // The host sizes the back-projection tile at 16 (mirrored) or 8 (plain)
     // bytes per entry, so at least one view's tile always fits.
+    // The column pitch is padded to 3, 5, 11 or 13 mod 16 words, which
+    // spreads lanes in neighbouring columns and rows over the banks (modelled
+    // clocks per wave instruction: 64-bit 8.2, 8.8 at 25; 32-bit 7.9-8.4,
+    // 11-12 at 1, 9 or 15 mod 16).
     TileShape tf = ts;
+    while (tf.tvp % 16 != 3 && tf.tvp % 16 != 5 && tf.tvp % 16 != 11 && tf.tvp % 16 != 13) tf.tvp += 2;
     const int64_t per_view =
-        static_cast<int64_t>(ts.tu + 1) * ts.tvp * sizeof(int) * (run.mirror ? 2 : 1);
+        static_cast<int64_t>(tf.tu + 1) * tf.tvp * sizeof(int) * (run.mirror ? 2 : 1);
     tf.vc = static_cast<int32_t>(std::min<int64_t>(kMaxStageViews, kTileLdsBytes / per_view));
     if (tf.vc < 1) return static_cast<int>(hipErrorInvalidValue);
     const size_t lds = static_cast<size_t>(tf.vc) * per_view;
-    if (run.mirror)
-      hipLaunchKernelGGL((fp_tiled_kernel<true>), grid, block, lds, st, gc, run, vb, tf, vol,
-                         q, vstride, scale, static_cast<int>(fixed_sums));
-    else
-      hipLaunchKernelGGL((fp_tiled_kernel<false>), grid, block, lds, st, gc, run, vb, tf, vol,
-                         q, vstride, scale, static_cast<int>(fixed_sums));
+    const auto kernel = run.mirror ? (ts.span >= kWalk ? &fp_mirror_kernel<true> : &fp_mirror_kernel<false>)
+                                   : (ts.span >= kWalk ? &fp_plain_kernel<true> : &fp_plain_kernel<false>);
+    hipLaunchKernelGGL(kernel, grid, block, lds, st, gc, run, fb, tf, vol, q, vstride, scale,
+                       static_cast<int>(fixed_sums));
   } else {
     const dim3 grid(static_cast<uint32_t>(nwg));
     if (run.mirror)
-      hipLaunchKernelGGL((fp_direct_kernel<true>), grid, block, 0, st, gc, run, vb, ts, vol, q,
+      hipLaunchKernelGGL((fp_direct_kernel<true>), grid, block, 0, st, gc, run, fb, ts, vol, q,
                          vstride, scale);
     else
-      hipLaunchKernelGGL((fp_direct_kernel<false>), grid, block, 0, st, gc, run, vb, ts, vol, q,
+      hipLaunchKernelGGL((fp_direct_kernel<false>), grid, block, 0, st, gc, run, fb, ts, vol, q,
                          vstride, scale);
   }
   return static_cast<int>(hipGetLastError());

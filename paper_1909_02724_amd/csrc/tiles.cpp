@@ -20,8 +20,6 @@ TileShape tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& 
                      const ViewBatch& vb, int32_t bz, int32_t entry_bytes, int32_t slots,
                      bool direct, bool bp_staging, bool read_pitch) {
   TileShape ts{};
-  ts.rot_a = 1;
-  ts.rot_b = 4;
   ts.nbx = (gc.nx + kBrickX - 1) / kBrickX;
   ts.nby = (gc.ny + kBrickY - 1) / kBrickY;
   ts.nseg = (run.n + bz - 1) / bz;

@@ -6,9 +6,16 @@
 // shape must fit the staged kernels' passes and LDS. The columns of a view
 // are walked on a sample of bricks.
 //
+// The adjoint's bounds are checked on the same bricks: its 8-slice walk stays in
+// its tile where the brick's corners allow it, and no pixel can receive from
+// more (column, slice) pairs than columns_at_pixel times slots_at_row, by a
+// histogram of the columns' pixels.
+//
 // Usage: row_walk_check SEED COUNT
 // Prints "<kind> launches=.. walked=.. columns=.. np16=.. np8=.. np4=..
-// groups=.. bad_shape=.. low=.. high=.. offset=..".
+// groups=.. bad_shape=.. low=.. high=.. offset=..
+// adj_bricks=.. adj_walked=.. adj_low=.. adj_high=.. adj_over=.. adj_slack=.."
+// (the mean of bound over histogram maximum, in per cent).
 #include <algorithm>
 #include <cinttypes>
 #include <cmath>
@@ -36,6 +43,8 @@ struct SplitMix64 {  // Steele, Lea and Flood (2014)
 struct Stats {
   long launches = 0, walked = 0, columns = 0, np[3] = {0, 0, 0}, groups = 0;
   long bad_shape = 0, low = 0, high = 0, offset = 0;
+  long adj_bricks = 0, adj_walked = 0, adj_low = 0, adj_high = 0, adj_over = 0;
+  double adj_slack = 0.0;  // sum of bound / histogram maximum
 };
 
 void check_run(const fdk_geometry& g, const fdk::GeoConst& gc, const fdk::SliceRun& run,
@@ -97,6 +106,56 @@ void check_run(const fdk_geometry& g, const fdk::GeoConst& gc, const fdk::SliceR
   }
 }
 
+void check_adjoint(const fdk_geometry& g, const fdk::GeoConst& gc, const fdk::SliceRun& run,
+                   const fdk::ViewBatch& vb, SplitMix64* rng, Stats* st) {
+  using namespace fdk;
+  const bool mirror = run.mirror != 0;
+  const int32_t bz = mirror ? kBrickZ : kPlainBrickZ, walk = kBrickZ / 2;
+  const TileShape ts = mirror ? tile_shape(&g, gc, run, vb, bz, kTileEntryBytes, kPrefetchSlots, false)
+                              : tile_shape(&g, gc, run, vb, bz, kPlainEntryBytes, 1 << 30, false);
+  if (ts.vc <= 0) return;
+  const float kvf = static_cast<float>(gc.kv);
+  for (int n = 0; n < 8; ++n) {
+    const int32_t s = rng->irange(0, vb.nviews - 1);
+    const int32_t bx = n < 4 ? (n & 1) * (ts.nbx - 1) : rng->irange(0, ts.nbx - 1);
+    const int32_t by = n < 4 ? (n >> 1) * (ts.nby - 1) : rng->irange(0, ts.nby - 1);
+    const int32_t kb = run.k_first + rng->irange(0, ts.nseg - 1) * bz;
+    const int32_t i_lo = bx * kBrickX, j_lo = by * kBrickY;
+    const int32_t i_hi = std::min(i_lo + kBrickX - 1, gc.nx - 1);
+    const int32_t j_hi = std::min(j_lo + kBrickY - 1, gc.ny - 1);
+    const ViewGeo vg = view_geo(gc, vb.sn[s], vb.cs[s]);
+    const BrickView b = brick_setup(gc, vg, i_lo, i_hi, j_lo, j_hi, kb, 0, 0, bz, mirror);
+    float drift = 0.0f, dvk = INFINITY;
+    for (int c = 0; c < 4; ++c) {
+      const ColumnF32 col = column_f32(b, (c & 1) ? static_cast<float>(i_hi - i_lo) : 0.0f,
+                                       (c & 2) ? static_cast<float>(j_hi - j_lo) : 0.0f, kvf);
+      drift = std::fmax(drift, std::fabs(col.eps));
+      dvk = std::fmin(dvk, col.dvk);
+    }
+    const bool walks = static_cast<float>(walk - 1) * drift <= static_cast<float>(kSpanDrift);
+    ++st->adj_bricks;
+    st->adj_walked += walks;
+    std::vector<float> hist(ts.tu + 2, 0.0f);
+    for (int32_t j = j_lo; j <= j_hi; ++j) {
+      for (int32_t i = i_lo; i <= i_hi; ++i) {
+        const ColumnF32 c = column_f32(b, static_cast<float>(i - i_lo), static_cast<float>(j - j_lo), kvf);
+        hist[std::min<uint32_t>(c.nu, ts.tu - 1) + 1] += slots_at_row(c.dvk, bz);
+        const float down = std::fmin(static_cast<float>(walk - 1) * c.eps, 0.0f);
+        for (int32_t k0 = 0; walks && k0 < bz; k0 += walk) {
+          const float fl = floorf(fmaf(static_cast<float>(k0), c.eps, c.vl) + down);
+          if (k0 + static_cast<int32_t>(fl) < 0) ++st->adj_low;
+          if (k0 + static_cast<int32_t>(fl) + walk + 1 >= ts.tv) ++st->adj_high;
+        }
+      }
+    }
+    float most = 0.0f;
+    for (size_t p = 1; p < hist.size(); ++p) most = std::fmax(most, hist[p] + hist[p - 1]);
+    const float bound = slots_at_row(dvk, bz) * static_cast<float>(columns_at_pixel(gc, vg, i_lo, i_hi, j_lo, j_hi));
+    if (bound < most) ++st->adj_over;
+    st->adj_slack += bound / most;
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -139,14 +198,19 @@ int main(int argc, char** argv) {
     if (gc.mirror_g != INT32_MIN && g.nz >= 2)
       check_run(g, gc, fdk::SliceRun{0, g.nz / 2, 0, g.nz - 1, 1}, vb, &rng, &all[0]);
     check_run(g, gc, fdk::SliceRun{0, g.nz, 0, 0, 0}, vb, &rng, &all[1]);
+    if (gc.mirror_g != INT32_MIN && g.nz >= 2)
+      check_adjoint(g, gc, fdk::SliceRun{0, g.nz / 2, 0, g.nz - 1, 1}, vb, &rng, &all[0]);
+    check_adjoint(g, gc, fdk::SliceRun{0, g.nz, 0, 0, 0}, vb, &rng, &all[1]);
   }
   const char* names[2] = {"mirror", "plain"};
   for (int k = 0; k < 2; ++k) {
     const Stats& s = all[k];
     std::printf("%s launches=%ld walked=%ld columns=%ld np16=%ld np8=%ld np4=%ld groups=%ld "
-                "bad_shape=%ld low=%ld high=%ld offset=%ld\n",
+                "bad_shape=%ld low=%ld high=%ld offset=%ld adj_bricks=%ld adj_walked=%ld adj_low=%ld "
+                "adj_high=%ld adj_over=%ld adj_slack=%ld\n",
                 names[k], s.launches, s.walked, s.columns, s.np[0], s.np[1], s.np[2], s.groups,
-                s.bad_shape, s.low, s.high, s.offset);
+                s.bad_shape, s.low, s.high, s.offset, s.adj_bricks, s.adj_walked, s.adj_low, s.adj_high,
+                s.adj_over, static_cast<long>(100.0 * s.adj_slack / std::max(1l, s.adj_bricks)));
   }
   return 0;
 }

@@ -93,3 +93,44 @@ def test_non_finite_pixels_reach_their_own_voxels_only(size, off_v):
     assert not fine.all()
     assert np.array_equal(fine, np.isfinite(got))
     assert rel_l2(got[fine], 0.5 + ref[fine]) <= 1e-5
+
+
+@pytest.mark.parametrize("off_v", [0.0, 0.27], ids=["mirrored", "plain"])
+@pytest.mark.parametrize("slope", [1.0, 1.12, 1.3], ids=["walk", "walk_edge", "single"])
+@pytest.mark.parametrize("size, views, cone", [("tiny", 1, 8.0), ("tiny", 13, 3.0), ("small", 7, 8.0),
+                                               ("medium", 97, 5.0), ("large", 3, 8.0)])
+def test_adjoint_walk_matches_oracle(size, views, cone, slope, off_v):
+    """The adjoint's row sums, in bricks that walk and bricks that take one
+    slice at a time, for views along both axes, against the oracle; and on a
+    volume of ones, where every pixel's sum comes closest to the fixed-point
+    bound (an overflow would wrap), to 2e-6 of it: FP32 rounding of the
+    coordinates and of the sums' few dozen adds."""
+    g = geom(SIZES[size], slope, off_v, cone=cone)
+    ang = synth.angles(views, start=0.6)
+    print(f"adjoint walk {size} views={views} cone={cone} slope={slope} off_v={off_v}", flush=True)
+    x = np.random.default_rng(views).standard_normal((g.nz, g.ny, g.nx)).astype(np.float32)
+    for vol, tol in ((x, 1e-5), (np.ones_like(x), 2e-6)):
+        ref = oracle.forward_project(g, ang, vol.astype(np.float64), scale=1.0e4)
+        got = fdk.forward_project(torch.from_numpy(vol).to(DEV), g, ang, scale=1.0e4)
+        err = rel_l2(host(got), ref)
+        print(f"  {err:.2e}", flush=True)
+        assert err <= tol
+        fdk.forward_project(torch.from_numpy(vol).to(DEV), g, ang, scale=1.0e4, out=got,
+                            accumulate=True)
+        assert rel_l2(host(got), 2.0 * ref) <= tol
+
+
+@pytest.mark.parametrize("magnitude", [1e-36, 1e-27, 1e36])
+def test_adjoint_at_the_ends_of_the_float_range(magnitude):
+    """The sums are scaled to the brick's largest voxel, so volumes near either
+    end of FP32's range project as accurately as others."""
+    g = geom((40, 33, 30), 1.0, 0.0)
+    ang = synth.angles(4, start=0.2)
+    x = np.random.default_rng(6).uniform(0.5, 1.0, (g.nz, g.ny, g.nx)).astype(np.float32)
+    ref = oracle.forward_project(g, ang, x.astype(np.float64))
+    got = fdk.forward_project(torch.from_numpy((x * np.float32(magnitude))).to(DEV), g, ang,
+                              scale=1.0)
+    # (projections of the smallest volumes are subnormal or zero in FP32)
+    floor = 2.0 ** -149 * 200 / magnitude
+    err = np.abs(host(got) / magnitude - ref).max()
+    assert err <= 1e-5 * ref.max() + floor

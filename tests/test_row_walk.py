@@ -1,4 +1,5 @@
-"""The back-projector's launch shapes and the rows its row walk reads.
+"""The back-projector's launch shapes, the rows its row walk reads, and the
+adjoint's walk and fixed-point bounds.
 
 A block of slices whose column drifts by less than a pixel against rows one
 apart takes all its taps from consecutive staged rows at fixed offsets from
@@ -40,4 +41,7 @@ def test_row_walk_stays_inside_the_tile(checker, seed):
         # Every brick height, several groups and enough walked columns occur.
         assert s["walked"] >= 500 and s["columns"] >= 500_000, (kind, s)
         assert min(s["np16"], s["np8"], s["np4"], s["groups"]) >= 50, (kind, s)
+        # The adjoint: walks in its tile, pixels within the bound, the bound not wide.
+        assert s["adj_walked"] >= 1000 and s["adj_slack"] <= 200, (kind, s)
+        assert s["adj_low"] == s["adj_high"] == s["adj_over"] == 0, (kind, s)
         assert s["bad_shape"] == s["low"] == s["high"] == s["offset"] == 0, (kind, s)
