@@ -32,7 +32,6 @@ namespace {
 
 constexpr int kFilterThreads = 256;
 constexpr int kFftMaxLog = 13;             // L <= 8192 complex points (132 KiB of LDS)
-constexpr int64_t kFftMaxGroups = 2048;    // workgroups of an FFT launch
 constexpr int kDirectMaxNu = 256;          // below this the direct kernel is cheaper
 constexpr int kDirectMaxLds = 8192;        // widest row of the direct kernel (2 x 64 KB of LDS)
 
@@ -150,12 +149,67 @@ hipError_t raise_lds_limit(size_t bytes) {
 // travel as the real and imaginary parts of one complex sequence: g is real,
 // so IFFT(FFT(a + i b) G) = (g * a) + i (g * b). The FFTs are radix-16
 // Stockham passes over points held in registers, exchanged through LDS
-// between passes, with each pass's twiddles read from a table of its own
-// (FP64 values rounded once); the inverse transform is the forward one of
-// the conjugate. Each workgroup computes the twiddle tables and G once and
-// then loops over row pairs; each pair's loads are unconditional and all in
-// flight together.
+// between passes, with each middle pass's twiddles read from a table of its own
+// in LDS and the last one's kept in registers (FP64 values rounded once, from
+// a table compiled in); the inverse transform is the forward one of the
+// conjugate. Each workgroup sets up the tables and G once and then loops over
+// row pairs; each pair's loads are unconditional and all in flight together.
 using cf = float2;
+
+// exp(-2 pi i m / 8192) for all m, FP64 values rounded once: the first octant
+// from the Taylor series of sine and cosine (|x| <= pi / 4: terms to x^19 leave
+// less than 1e-18), the rest by symmetry.
+constexpr int kTwiddles = 1 << kFftMaxLog;
+struct TwiddleTable {
+  float x[kTwiddles], y[kTwiddles];
+  constexpr TwiddleTable() : x(), y() {
+    constexpr int n = kTwiddles, q = n / 4, o = n / 8;
+    double c[o + 1] = {}, s[o + 1] = {};
+    for (int m = 0; m <= o; ++m) {
+      const double a = 6.283185307179586476925 * m / n, a2 = a * a;
+      double cs = 1.0, sn = 1.0;
+      for (int k = 18; k >= 2; k -= 2) {
+        cs = 1.0 - cs * a2 / (k * (k - 1));
+        sn = 1.0 - sn * a2 / (k * (k + 1));
+      }
+      c[m] = cs;
+      s[m] = sn * a;
+    }
+    for (int m = 0; m < n; ++m) {
+      const int r = m % q, quarter = m / q;
+      const double cr = r <= o ? c[r] : s[q - r], sr = r <= o ? s[r] : c[q - r];
+      const double cc = quarter == 0 ? cr : quarter == 1 ? -sr : quarter == 2 ? -cr : sr;
+      const double ss = quarter == 0 ? sr : quarter == 1 ? cr : quarter == 2 ? -sr : -cr;
+      x[m] = static_cast<float>(cc);
+      y[m] = static_cast<float>(-ss);
+    }
+  }
+};
+__device__ constexpr TwiddleTable kTwiddle{};
+__device__ __forceinline__ cf twiddle(int32_t m) {
+  return make_float2(kTwiddle.x[m & (kTwiddles - 1)], kTwiddle.y[m & (kTwiddles - 1)]);
+}
+
+// Sums of the odd 1 / j^2 up to n (the Ram-Lak taps), n < 4096.
+constexpr int kOddSums = 1 << (kFftMaxLog - 1);
+struct OddSums {
+  double v[kOddSums];
+  constexpr OddSums() : v() {
+    double s = 0.0;
+    for (int j = 1; j < kOddSums; ++j) {
+      if (j % 2) s += 1.0 / (static_cast<double>(j) * j);
+      v[j] = s;
+    }
+  }
+};
+__device__ constexpr OddSums kOddSum{};
+
+// tau times the sum of the ramp taps h(1) ... h(n) (ramp_tap).
+__device__ __forceinline__ double ramp_sum(int kind, int32_t n, double tau) {
+  const double pi = 3.14159265358979323846;
+  if (kind == FDK_RAMLAK) return -kOddSum.v[n] / (pi * pi * tau);
+  return -2.0 / (pi * pi * tau) * n / (2.0 * n + 1.0);  // the sum telescopes
+}
 
 template <int LOGL>
 struct FftCfg {
@@ -176,7 +230,22 @@ struct FftCfg {
     for (int q = 1; q < p; ++q) off += 15 * ns(q);
     return off;
   }
-  static constexpr int TW = tw_off(NP);
+  static constexpr int TW = tw_off(NP - 1);
+  // Three waves per SIMD (168 VGPRs) hold a thread's 16 points and the last
+  // pass's twiddles, but not its 16 points of conj(G) / L, which are then read
+  // from LDS (points 0 to L / 2; the others are their conjugates). At L = 8192
+  // that table and the buffer leave one workgroup a CU, two waves per SIMD,
+  // which hold conj(G) in registers. 128 views of 2048^2: 1.80 ms before, 1.67
+  // with two waves and conj(G) in registers, 1.55 with three (four spill:
+  // 1.98); 0.86 ms is a copy's time. 16 views x 289 rows of 4096: 255 -> 98
+  // us, nearly all from the set-up (see launch_fft); two workgroups a CU spill
+  // (121 us).
+  static constexpr bool G_LDS = LOGL < 13;
+  static constexpr int GTAB = G_LDS ? L / 2 + 1 : 0;
+  static constexpr int LDS = (G * BUF + TW + GTAB) * static_cast<int>(sizeof(cf));
+  // Workgroups resident on a CU: its 160 KB of LDS and the kernel's waves.
+  static constexpr int WAVES = G_LDS ? 3 : 2;
+  static constexpr int PER_CU = std::min(163840 / LDS, WAVES * 4 * 64 / WG);
 };
 
 template <int LOGL, int IP>
@@ -245,7 +314,8 @@ __device__ __forceinline__ void dft_reg(cf* v) {
 }
 
 // v[r] *= W^(r k) for r in [1, 16), read from the pass's table (NS
-// entries per r; the thread's j = t mod NS picks k = j L / (16 NS)).
+// entries per r; the thread's j = t mod NS picks k = j L / (16 NS)). In the
+// last pass j = t: the thread's fifteen stay in its registers.
 template <int NS>
 __device__ __forceinline__ void apply_twiddles(cf* v, const cf* tab, int32_t j) {
 #pragma unroll
@@ -255,7 +325,7 @@ __device__ __forceinline__ void apply_twiddles(cf* v, const cf* tab, int32_t j) 
 // Input index of point (m, r) of pass IP for thread t: butterfly
 // j = t + m TPF, element r, index j + r L / R.
 template <int LOGL, int IP>
-__device__ __forceinline__ int32_t gather_index(int32_t t, int m, int r) {
+__device__ __forceinline__ constexpr int32_t gather_index(int32_t t, int m, int r) {
   using P = PassCfg<LOGL, IP>;
   return t + m * FftCfg<LOGL>::TPF + r * (FftCfg<LOGL>::L / P::R);
 }
@@ -282,31 +352,45 @@ __device__ __forceinline__ constexpr int last_of_first(int i) {
 // NS > 1 are radix 16 with one butterfly per thread (j = t), twiddle
 // exponent k = (t mod NS) L / (16 NS).
 template <int LOGL, int IP>
-__device__ __forceinline__ void pass_compute(cf* v, int32_t t, const cf* tw) {
+__device__ __forceinline__ void pass_compute(cf* v, int32_t t, const cf* tw, const cf* last) {
   using P = PassCfg<LOGL, IP>;
-  if constexpr (P::NS > 1)
+  if constexpr (IP + 1 == FftCfg<LOGL>::NP) {
+#pragma unroll
+    for (int r = 1; r < 16; ++r) v[r] = cmul(v[r], last[r - 1]);
+  } else if constexpr (P::NS > 1) {
     apply_twiddles<P::NS>(v, tw + FftCfg<LOGL>::tw_off(IP), t % P::NS);
+  }
 #pragma unroll
   for (int m = 0; m < P::B; ++m) dft_reg<P::R>(v + m * P::R);
 }
 
+// Padded buffer places of a thread's points: one computed base a pass and
+// constant offsets. (Every step below is a multiple of 16, or stays inside a
+// block of 16, so the padding of a sum is the sum of the paddings; written per
+// point, the compiler keeps an address register for each, 40 to 60 in all.)
+constexpr int32_t pad_of(int32_t i) { return i + (i >> 4); }
+
 template <int LOGL, int IP>
 __device__ __forceinline__ void pass_scatter_lds(cf* buf, int32_t t, const cf* v) {
   using P = PassCfg<LOGL, IP>;
+  static_assert(P::NS % 16 == 0 || 16 % P::NS == 0, "a step keeps to blocks of 16");
+  static_assert(FftCfg<LOGL>::TPF % 16 == 0, "a butterfly's step is a multiple of 16 points");
+  cf* const base = buf + fpad(scatter_index<LOGL, IP>(t, 0));
 #pragma unroll
   for (int m = 0; m < P::B; ++m)
 #pragma unroll
     for (int r = 0; r < P::R; ++r)
-      buf[fpad(scatter_index<LOGL, IP>(t + m * FftCfg<LOGL>::TPF, r))] = v[m * P::R + r];
+      base[pad_of(m * FftCfg<LOGL>::TPF * P::R) + pad_of(r * P::NS)] = v[m * P::R + r];
 }
 
 template <int LOGL, int IP>
 __device__ __forceinline__ void pass_gather_lds(const cf* buf, int32_t t, cf* v) {
   using P = PassCfg<LOGL, IP>;
+  const cf* const base = buf + fpad(t);
 #pragma unroll
   for (int m = 0; m < P::B; ++m)
 #pragma unroll
-    for (int r = 0; r < P::R; ++r) v[m * P::R + r] = buf[fpad(gather_index<LOGL, IP>(t, m, r))];
+    for (int r = 0; r < P::R; ++r) v[m * P::R + r] = base[pad_of(gather_index<LOGL, IP>(0, m, r))];
 }
 
 // Passes IP..NP-1 of a transform whose points sit in v (already gathered
@@ -314,14 +398,14 @@ __device__ __forceinline__ void pass_gather_lds(const cf* buf, int32_t t, cf* v)
 // scatter_index; every earlier pass crosses LDS, behind a barrier that also
 // orders it after the buffer's previous reads.
 template <int LOGL, int IP>
-__device__ __forceinline__ void fft_rest(cf* buf, int32_t t, cf* v, const cf* tw) {
-  pass_compute<LOGL, IP>(v, t, tw);
+__device__ __forceinline__ void fft_rest(cf* buf, int32_t t, cf* v, const cf* tw, const cf* last) {
+  pass_compute<LOGL, IP>(v, t, tw, last);
   if constexpr (IP + 1 < FftCfg<LOGL>::NP) {
     __syncthreads();
     pass_scatter_lds<LOGL, IP>(buf, t, v);
     __syncthreads();
     pass_gather_lds<LOGL, IP + 1>(buf, t, v);
-    fft_rest<LOGL, IP + 1>(buf, t, v, tw);
+    fft_rest<LOGL, IP + 1>(buf, t, v, tw, last);
   }
 }
 
@@ -394,7 +478,8 @@ __device__ __forceinline__ float row_diff(__amdgpu_buffer_rsrc_t r, RowWeight rw
 }
 
 template <int LOGL, typename OutT, bool ADJ>
-__global__ __launch_bounds__(FftCfg<LOGL>::WG) void filter_fft_kernel(
+__global__ __launch_bounds__(FftCfg<LOGL>::WG) __attribute__((amdgpu_waves_per_eu(FftCfg<LOGL>::WAVES, FftCfg<LOGL>::WAVES)))
+void filter_fft_kernel(
     GeoConst gc, RowBand rband, double du, double dv, double sdd, double tau, int kind,
     int64_t nrows, const float* __restrict__ e, OutT* __restrict__ q) {
   using C = FftCfg<LOGL>;
@@ -408,52 +493,21 @@ __global__ __launch_bounds__(FftCfg<LOGL>::WG) void filter_fft_kernel(
   const ColConst cc{static_cast<float>(gc.cu), static_cast<float>(du), static_cast<float>(sdd),
                     static_cast<float>(-sdd * du)};
 
+  // Twiddles: the middle passes' tables in LDS, the last pass's in registers.
   for (int32_t i = threadIdx.x; i < C::TW; i += C::WG) {
     int p = 1;
-    while (p + 1 < C::NP && i >= C::tw_off(p + 1)) ++p;
+    while (p + 2 < C::NP && i >= C::tw_off(p + 1)) ++p;
     const int32_t ns = C::ns(p), rel = i - C::tw_off(p);
-    const int32_t m = (rel / ns + 1) * (rel % ns) * (C::L / (16 * ns));  // < L
-    double sv, cv;
-    sincospi(-2.0 * static_cast<double>(m) / C::L, &sv, &cv);
-    tw[i] = make_float2(static_cast<float>(cv), static_cast<float>(sv));
+    tw[i] = twiddle((rel / ns + 1) * (rel % ns) * (kTwiddles / (16 * ns)));
   }
+  cf last[15];
+#pragma unroll
+  for (int r = 1; r < 16; ++r) last[r - 1] = twiddle(r * t * (kTwiddles / C::L));
 
-  // g(m) for m in [-N, N), FP64, at dg[m + N]: an inclusive scan of the
-  // taps over the workgroup (consecutive chunks per thread, then the chunk
-  // totals), in the FFT buffers: their G (L + L/16) points of 8 bytes hold
-  // the 2N + WG doubles (L >= 2N and G L / 16 = WG).
-  double* dg = reinterpret_cast<double*>(fbuf);
-  double* part = dg + 2 * nu;
-  {
-    const int32_t n2 = 2 * nu;
-    const int32_t chunk = (n2 + C::WG - 1) / C::WG;
-    const int32_t k0 = static_cast<int32_t>(threadIdx.x) * chunk;
-    double s = 0.0;
-    for (int32_t j = 0; j < chunk; ++j) {
-      const int32_t k = k0 + j;
-      if (k < n2) {
-        if (k > 0) s += tau * ramp_tap(kind, k - nu, tau);
-        dg[k] = s;
-      }
-    }
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int32_t off = 1; off < C::WG; off *= 2) {
-      const double p = threadIdx.x >= static_cast<uint32_t>(off) ? part[threadIdx.x - off] : 0.0;
-      __syncthreads();
-      part[threadIdx.x] += p;
-      __syncthreads();
-    }
-    const double before = threadIdx.x > 0 ? part[threadIdx.x - 1] : 0.0;
-    for (int32_t j = 0; j < chunk; ++j) {
-      const int32_t k = k0 + j;
-      if (k < n2) dg[k] += before;
-    }
-    __syncthreads();
-  }
-
-  // G: FFT of g placed circularly (index m mod L). Each thread keeps
-  // conj(G) / L at the points it gathers in a transform's first pass.
+  // G: FFT of g placed circularly (index m mod L), g from the taps' closed or
+  // tabulated sums in FP64. Each thread keeps conj(G) / L at the points it
+  // gathers in a transform's first pass.
+  const double total = ramp_sum(kind, nu - 1, tau), centre = tau * ramp_tap(kind, 0, tau);
   cf v[16];
 #pragma unroll
   for (int m = 0; m < B0; ++m)
@@ -461,19 +515,43 @@ __global__ __launch_bounds__(FftCfg<LOGL>::WG) void filter_fft_kernel(
     for (int r = 0; r < R0; ++r) {
       const int32_t n = gather_index<LOGL, 0>(t, m, r);
       const int32_t s = n < C::L / 2 ? n : n - C::L;
-      const float gv = (s >= -nu && s < nu) ? static_cast<float>(dg[s + nu]) : 0.0f;
+      float gv = 0.0f;
+      if (s >= -nu && s < nu)
+        gv = static_cast<float>(s >= 0 ? total + centre + ramp_sum(kind, s, tau)
+                                       : total - ramp_sum(kind, -s - 1, tau));
       v[m * R0 + r] = make_float2(gv, 0.0f);
     }
-  fft_rest<LOGL, 0>(buf, t, v, tw);  // its first barrier follows every read of dg
-  cf gc_[16];
-  {
-    constexpr float inv_l = 1.0f / static_cast<float>(C::L);  // a power of two: exact
+  __syncthreads();  // the tables
+  fft_rest<LOGL, 0>(buf, t, v, tw, last);
+  constexpr float inv_l = 1.0f / static_cast<float>(C::L);  // a power of two: exact
+  // The last pass leaves point t + i TPF in register i, which the inverse
+  // transform's first pass takes as its register i' (last_of_first).
+  cf* const gtab = tw + C::TW;
+  cf gc_[C::G_LDS ? 1 : 16];
+  if constexpr (C::G_LDS) {
+#pragma unroll
+    for (int i = 0; i <= 8; ++i) {
+      const int32_t k = t + i * C::TPF;
+      if (g == 0 && k <= C::L / 2) gtab[k] = make_float2(v[i].x * inv_l, -v[i].y * inv_l);
+    }
+    __syncthreads();
+  } else {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const cf x = v[last_of_first<LOGL>(i)];
       gc_[i] = make_float2(x.x * inv_l, -x.y * inv_l);
     }
   }
+  auto conj_g = [&](int i) {  // at the point of the inverse's register i
+    if constexpr (C::G_LDS) {
+      const int j = last_of_first<LOGL>(i);
+      if (j < 8) return gtab[t + j * C::TPF];
+      const cf x = gtab[C::L - t - j * C::TPF];
+      return make_float2(x.x, -x.y);
+    } else {
+      return gc_[i];
+    }
+  };
 
   // Row pairs are wave-uniform (an FFT spans whole waves), so each row is
   // addressed through a buffer descriptor: pixels at or beyond Nu, and rows
@@ -517,16 +595,16 @@ __global__ __launch_bounds__(FftCfg<LOGL>::WG) void filter_fft_kernel(
       const int32_t n = gather_index<LOGL, 0>(t, 0, R0 / 2);
       v[R0 / 2] = make_float2(row_diff<ADJ>(ia, wa, cc, n), row_diff<ADJ>(ib, wb, cc, n));
     }
-    fft_rest<LOGL, 0>(buf, t, v, tw);
+    fft_rest<LOGL, 0>(buf, t, v, tw, last);
     // Inverse: the forward transform of conj(Y G) / L, taken in registers
     // (the last pass's points are the first pass's).
     cf z[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const cf y = v[last_of_first<LOGL>(i)];
-      z[i] = cmul(make_float2(y.x, -y.y), gc_[i]);
+      z[i] = cmul(make_float2(y.x, -y.y), conj_g(i));
     }
-    fft_rest<LOGL, 0>(buf, t, z, tw);
+    fft_rest<LOGL, 0>(buf, t, z, tw, last);
     // The last pass has one radix-16 butterfly per thread (j = t, NS = L/16):
     // result j is point t + j L/16, so the stores are coalesced; only the
     // lower half (j < 8) holds row pixels.
@@ -558,17 +636,22 @@ template <int LOGL, typename OutT, bool ADJ>
 int launch_fft(const GeoConst& gc, const RowBand& rb, double du, double dv, double sdd, double tau,
                int kind, int64_t nrows, const float* e, OutT* q, hipStream_t st) {
   using C = FftCfg<LOGL>;
-  const size_t lds = (static_cast<size_t>(C::G) * C::BUF + C::TW) * sizeof(cf);
+  const size_t lds = C::LDS;
   auto kern = &filter_fft_kernel<LOGL, OutT, ADJ>;
   if (lds > 65536) {
     const hipError_t err = raise_lds_limit<&filter_fft_kernel<LOGL, OutT, ADJ>>(lds);
     if (err != hipSuccess) return static_cast<int>(err);
   }
-  // Workgroups loop over row pairs (G is computed once per workgroup): a
-  // few per CU at most.
+  // Workgroups loop over row pairs (tables and G are set up once per
+  // workgroup): no more of them than are resident at once, evenly loaded. (Up
+  // to 2048 workgroups, each with its own FP64 sines and scan of the taps,
+  // took 255 us for 2312 row pairs of 4096 pixels; 512 took 135; as here, with
+  // the tables compiled in, 98.)
   const int64_t npairs = (nrows + 1) / 2;
   const int64_t want = (npairs + C::G - 1) / C::G;
-  const uint32_t groups = static_cast<uint32_t>(std::min<int64_t>(want, kFftMaxGroups));
+  const int64_t resident = int64_t{kCus} * C::PER_CU;
+  const int64_t passes = (want + resident - 1) / resident;
+  const uint32_t groups = static_cast<uint32_t>((want + passes - 1) / passes);
   hipLaunchKernelGGL(kern, dim3(groups), dim3(C::WG), lds, st, gc, rb, du, dv, sdd, tau, kind,
                      nrows, e, q);
   return static_cast<int>(hipGetLastError());
