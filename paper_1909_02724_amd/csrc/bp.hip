@@ -566,9 +566,9 @@ __device__ __forceinline__ bool bp_staged_body(const GeoConst& gc, const SliceRu
   const uint32_t row_es = static_cast<uint32_t>(gc.nu) * es;
   const uint32_t nrec = static_cast<uint32_t>(gc.nu) * static_cast<uint32_t>(gc.nv) * es;
   const uint32_t t_main =
-      loader ? static_cast<uint32_t>(sr) * row_es + static_cast<uint32_t>(sc) * es : kBadRow;
+      loader ? static_cast<uint32_t>(sr) * row_es + static_cast<uint32_t>(sc) * es : kBadLane;
   const uint32_t t_mir =
-      loader ? static_cast<uint32_t>(sc) * es - static_cast<uint32_t>(sr) * row_es : kBadRow;
+      loader ? static_cast<uint32_t>(sc) * es - static_cast<uint32_t>(sr) * row_es : kBadLane;
   const uint32_t step = static_cast<uint32_t>(rstep) * row_es;
   const uint32_t lds_lane = static_cast<uint32_t>(sc * tvp + sr);
   uint32_t pre[ROWS], prem[ROWS];  // raw bits of q(u) of each pass's row and mirror row
@@ -579,35 +579,23 @@ __device__ __forceinline__ bool bp_staged_body(const GeoConst& gc, const SliceRu
     const int32_t inside = __builtin_amdgcn_readfirstlane(b.inside);
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<T*>(q + s * vstride), 0, nrec, kBufferWord3);
-    uint32_t o[ROWS], m[ROWS];
-    if (inside) {
-      const uint32_t off = t_main + (static_cast<uint32_t>(org_v) * row_es + static_cast<uint32_t>(org_u) * es);
-      const uint32_t offm = t_mir + (static_cast<uint32_t>(MIRROR ? gc.mirror_g - org_v : 0) * row_es +
-                                     static_cast<uint32_t>(org_u) * es);
-#pragma unroll
-      for (int rr = 0; rr < ROWS; ++rr) {
-        o[rr] = off + static_cast<uint32_t>(rr) * step;
-        m[rr] = offm - static_cast<uint32_t>(rr) * step;
-      }
-    } else {
-      const int32_t gu = org_u + sc;
-      const uint32_t c0 = loader && static_cast<uint32_t>(gu) < static_cast<uint32_t>(gc.nu)
-                              ? static_cast<uint32_t>(gu) * es : kBadCol;
-#pragma unroll
-      for (int rr = 0; rr < ROWS; ++rr) {
-        const int32_t gr = org_v + rr * rstep + sr;
-        const int32_t gm = MIRROR ? gc.mirror_g - gr : -1;
-        o[rr] = c0 + (static_cast<uint32_t>(gr) < static_cast<uint32_t>(gc.nv)
-                          ? static_cast<uint32_t>(gr) * row_es : kBadRow);
-        m[rr] = c0 + (static_cast<uint32_t>(gm) < static_cast<uint32_t>(gc.nv)
-                          ? static_cast<uint32_t>(gm) * row_es : kBadRow);
-      }
+    StageOrigin at = {org_u, org_v, MIRROR ? gc.mirror_g - org_v : 0};
+    uint32_t lane_main = t_main, lane_mir = t_mir;
+    if (!inside) {
+      // Rows off the detector fall out of the buffer's range, columns would not.
+      at = stage_origin(gc, org_u, org_v, rows * rstep, MIRROR);
+      const bool on = static_cast<uint32_t>(at.u + sc) < static_cast<uint32_t>(gc.nu);
+      lane_main = on ? t_main : kBadLane;
+      lane_mir = on ? t_mir : kBadLane;
     }
+    const uint32_t off = stage_offset(lane_main, at.u, at.v, row_es, es);
+    const uint32_t offm = stage_offset(lane_mir, at.u, at.vm, row_es, es);
 #pragma unroll
     for (int rr = 0; rr < ROWS; ++rr) {
       if (EXACT || rr < rows) {
-        pre[rr] = buf_load_raw<T>(rsrc, o[rr], 0);
-        if constexpr (MIRROR) prem[rr] = buf_load_raw<T>(rsrc, m[rr], 0);
+        pre[rr] = buf_load_raw<T>(rsrc, off + static_cast<uint32_t>(rr) * step, 0);
+        if constexpr (MIRROR)
+          prem[rr] = buf_load_raw<T>(rsrc, offm - static_cast<uint32_t>(rr) * step, 0);
       }
     }
   };
@@ -735,7 +723,7 @@ void bp_staged_kernel(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,
   extern __shared__ float4 tile[];
   __shared__ BrickView bvs[kMaxViewsPerLaunch];
   __shared__ int32_t nonfinite;
-  if (bp_staged_body<T, MIRROR, SPAN, kBrickZ, stage_passes(MIRROR, false), true, false>(
+  if (bp_staged_body<T, MIRROR, SPAN, kBrickZ, stage_passes(MIRROR, 0), true, false>(
           gc, run, vb, ts, q, vstride, vol, scale, accumulate, tile, bvs, &nonfinite))
     return;
   if constexpr (SPAN > 0) {
@@ -753,7 +741,7 @@ void bp_groups_kernel(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,
   extern __shared__ float4 tile[];
   __shared__ BrickView bvs[kMaxViewsPerLaunch];
   __shared__ int32_t nonfinite;
-  if (bp_staged_body<T, MIRROR, SPAN, NP, stage_passes(MIRROR, true), false, true>(
+  if (bp_staged_body<T, MIRROR, SPAN, NP, stage_passes(MIRROR, NP), false, true>(
           gc, run, vb, ts, q, vstride, vol, scale, accumulate, tile, bvs, &nonfinite))
     return;
   if constexpr (SPAN > 0) {

@@ -93,6 +93,30 @@ __host__ __device__ inline BrickView brick_setup(const GeoConst& gc, const ViewG
   return b;
 }
 
+// Where a staged tile is read from: its first column and row and the mirror of
+// its first row, drawn in to at most one tile (reach rows) off the detector, so
+// that every row off it lies off the buffer as well: above it at an offset
+// below zero, which wraps, and below it at or past the end. stage_reach_ok keeps
+// both, and lanes that start from kBadLane, within 32 bits.
+constexpr uint32_t kBadLane = 0x80000000u;
+struct StageOrigin {
+  int32_t u, v, vm;
+};
+__host__ __device__ __forceinline__ int32_t clamp_i32(int32_t x, int32_t lo, int32_t hi) {
+  return x < lo ? lo : x > hi ? hi : x;
+}
+__host__ __device__ __forceinline__ StageOrigin stage_origin(const GeoConst& gc, int32_t org_u,
+                                                             int32_t org_v, int32_t reach,
+                                                             bool mirror) {
+  return StageOrigin{clamp_i32(org_u, -kBrickThreads, gc.nu), clamp_i32(org_v, -reach, gc.nv),
+                     mirror ? clamp_i32(gc.mirror_g - org_v, -1, gc.nv + reach) : 0};
+}
+// Offset of a lane's pixel in pass 0; lane is its own part, row * row_es + column * es.
+__host__ __device__ __forceinline__ uint32_t stage_offset(uint32_t lane, int32_t u, int32_t row,
+                                                          uint32_t row_es, uint32_t es) {
+  return lane + (static_cast<uint32_t>(row) * row_es + static_cast<uint32_t>(u) * es);
+}
+
 // FP32 column quantities of one view for a thread at (tx, ty) in the brick.
 struct ColumnF32 {
   uint32_t nu, nvb;  // tile column and first row (relative to the origin)

@@ -88,7 +88,8 @@ TileShape tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& 
 // sums is latency: there
 //  - bricks shrink to 8 or 4 slices while they number at most one a CU
 //    (96^3 from 90 views: 59 us at 16 slices, 71 at 4 (432 bricks), 46 at 8
-//    (216); 80^3: 50 at 16, 39 at 4; 64^3 from 64 views: 91 -> 31 with groups);
+//    (216); 80^3: 50 at 16, 39 at 4; 64^3 from 64 views: 91 -> 31 with groups; all of
+//    these then with as many staging passes in the code as 16 slices need);
 //  - groups of threads share a brick's views: 4 up to a brick a CU, which
 //    fills it with 16 waves (128^3 from 180 views, 256 bricks: 238 -> 119 us,
 //    147 with two), 2 up to 1.5 (500 bricks: 192 us with one, 201 with two;
@@ -117,7 +118,8 @@ TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRu
   };
   auto bricks = [](const TileShape& t) { return static_cast<int64_t>(t.nbx) * t.nby * t.nseg; };
   auto staged = [&](const TileShape& t) {
-    return t.vc > 0 && t.rows <= stage_passes(run.mirror, true) && lds(t, 1) <= kGroupLdsBytes;
+    return t.vc > 0 && t.rows <= stage_passes(run.mirror, t.np) && lds(t, 1) <= kGroupLdsBytes &&
+           stage_reach_ok(g->nu, g->nv, t.rows * t.rstep);
   };
   TileShape ts = shape(kBrickZ);
   if (ts.vc <= 0) return ts;
@@ -134,7 +136,7 @@ TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRu
     ts.groups /= 2;
   ts.lds_bytes = lds(ts, ts.groups);
   ts.wide = ts.wide || ts.groups > 1 || ts.np != kBrickZ || ts.vc != kBpStageViews ||
-            ts.rows != stage_passes(run.mirror, false);
+            ts.rows != stage_passes(run.mirror, 0);
   return ts;
 }
 

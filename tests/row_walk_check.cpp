@@ -13,7 +13,7 @@
 //
 // Usage: row_walk_check SEED COUNT
 // Prints "<kind> launches=.. walked=.. columns=.. np16=.. np8=.. np4=..
-// groups=.. bad_shape=.. low=.. high=.. offset=..
+// groups=.. bad_shape=.. load=.. low=.. high=.. offset=..
 // adj_bricks=.. adj_walked=.. adj_low=.. adj_high=.. adj_over=.. adj_slack=.."
 // (the mean of bound over histogram maximum, in per cent).
 #include <algorithm>
@@ -42,7 +42,7 @@ struct SplitMix64 {  // Steele, Lea and Flood (2014)
 
 struct Stats {
   long launches = 0, walked = 0, columns = 0, np[3] = {0, 0, 0}, groups = 0;
-  long bad_shape = 0, low = 0, high = 0, offset = 0;
+  long bad_shape = 0, load = 0, low = 0, high = 0, offset = 0;
   long adj_bricks = 0, adj_walked = 0, adj_low = 0, adj_high = 0, adj_over = 0;
   double adj_slack = 0.0;  // sum of bound / histogram maximum
 };
@@ -60,16 +60,43 @@ void check_run(const fdk_geometry& g, const fdk::GeoConst& gc, const fdk::SliceR
   ++st->np[ts.np == kBrickZ ? 0 : ts.np == kMidBrickZ ? 1 : 2];
   if (ts.groups > 1) ++st->groups;
   const bool five = !ts.wide;
-  if (ts.rows > stage_passes(mirror, true) || ts.rows * ts.rstep < ts.tv ||
+  if (ts.rows > stage_passes(mirror, ts.np) || ts.rows * ts.rstep < ts.tv ||
       ts.lds_bytes < 2 * ts.groups * ts.tu * ts.tvp * entry ||
       ts.lds_bytes < ts.vc * ts.tu * ts.tvp * entry ||
       ts.lds_bytes < (ts.groups - 1) * ts.np * kBrickThreads * 4 || 
       ts.lds_bytes + kMaxViewsPerLaunch * static_cast<int>(sizeof(BrickView)) + 64 > 160 * 1024 ||
       ts.groups > kMaxGroups || ts.groups > vb.nviews || ts.nseg != (run.n + bz - 1) / bz ||
-      (five && (ts.np != kBrickZ || ts.groups != 1 || ts.rows != stage_passes(mirror, false) ||
+      (five && (ts.np != kBrickZ || ts.groups != 1 || ts.rows != stage_passes(mirror, 0) ||
                 ts.lds_bytes > kBpTileLdsBytes)) ||
       (span && bz % span))
     ++st->bad_shape;
+  // The staged loads' offsets (bp_staged_body): in the buffer exactly where the
+  // pixel and its mirror are on the detector, and then theirs.
+  for (int n = 0; n < 4; ++n) {
+    const int32_t s = rng->irange(0, vb.nviews - 1), seg = rng->irange(0, ts.nseg - 1);
+    const int32_t i_lo = rng->irange(0, ts.nbx - 1) * kBrickX, j_lo = rng->irange(0, ts.nby - 1) * kBrickY;
+    const BrickView b = brick_setup(gc, view_geo(gc, vb.sn[s], vb.cs[s]), i_lo,
+                                    std::min(i_lo + kBrickX - 1, gc.nx - 1), j_lo,
+                                    std::min(j_lo + kBrickY - 1, gc.ny - 1),
+                                    run.k_first + seg * bz, ts.tu, ts.tv, bz, mirror);
+    StageOrigin at = {b.org_u, b.org_v, mirror ? gc.mirror_g - b.org_v : 0};
+    if (!b.inside) at = stage_origin(gc, b.org_u, b.org_v, ts.rows * ts.rstep, mirror);
+    const uint32_t es = n & 1 ? 2 : 4, row_es = gc.nu * es, nrec = row_es * gc.nv;
+    for (int32_t r = 0; r < ts.tv; ++r) {
+      for (int32_t col = 0; col <= ts.tu; ++col) {
+        const int32_t u = b.org_u + col, v = b.org_v + r, vm = mirror ? gc.mirror_g - v : -1;
+        const int32_t sr = r % ts.rstep, pass = r / ts.rstep;
+        const bool on = b.inside || static_cast<uint32_t>(at.u + col) < static_cast<uint32_t>(gc.nu);
+        const uint32_t down = pass * ts.rstep * row_es;
+        const uint32_t o = stage_offset(on ? sr * row_es + col * es : kBadLane, at.u, at.v, row_es, es) + down;
+        const uint32_t m = stage_offset(on ? col * es - sr * row_es : kBadLane, at.u, at.vm, row_es, es) - down;
+        const bool in_u = u >= 0 && u < gc.nu;
+        const bool want = in_u && v >= 0 && v < gc.nv, want_m = in_u && vm >= 0 && vm < gc.nv;
+        if (want ? o != v * row_es + u * es : o < nrec) ++st->load;
+        if (mirror && (want_m ? m != vm * row_es + u * es : m < nrec)) ++st->load;
+      }
+    }
+  }
   if (span == 0) return;
   ++st->walked;
   const float kvf = static_cast<float>(gc.kv);
@@ -206,10 +233,10 @@ int main(int argc, char** argv) {
   for (int k = 0; k < 2; ++k) {
     const Stats& s = all[k];
     std::printf("%s launches=%ld walked=%ld columns=%ld np16=%ld np8=%ld np4=%ld groups=%ld "
-                "bad_shape=%ld low=%ld high=%ld offset=%ld adj_bricks=%ld adj_walked=%ld adj_low=%ld "
+                "bad_shape=%ld load=%ld low=%ld high=%ld offset=%ld adj_bricks=%ld adj_walked=%ld adj_low=%ld "
                 "adj_high=%ld adj_over=%ld adj_slack=%ld\n",
                 names[k], s.launches, s.walked, s.columns, s.np[0], s.np[1], s.np[2], s.groups,
-                s.bad_shape, s.low, s.high, s.offset, s.adj_bricks, s.adj_walked, s.adj_low, s.adj_high,
+                s.bad_shape, s.load, s.low, s.high, s.offset, s.adj_bricks, s.adj_walked, s.adj_low, s.adj_high,
                 s.adj_over, static_cast<long>(100.0 * s.adj_slack / std::max(1l, s.adj_bricks)));
   }
   return 0;

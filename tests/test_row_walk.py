@@ -44,4 +44,4 @@ def test_row_walk_stays_inside_the_tile(checker, seed):
         # The adjoint: walks in its tile, pixels within the bound, the bound not wide.
         assert s["adj_walked"] >= 1000 and s["adj_slack"] <= 200, (kind, s)
         assert s["adj_low"] == s["adj_high"] == s["adj_over"] == 0, (kind, s)
-        assert s["bad_shape"] == s["low"] == s["high"] == s["offset"] == 0, (kind, s)
+        assert s["bad_shape"] == s["load"] == s["low"] == s["high"] == s["offset"] == 0, (kind, s)
