@@ -343,13 +343,7 @@ fdk_status fdk_forward_project(const fdk_geometry* g, int32_t view0, int32_t nvi
     const int32_t n = std::min(per, nviews - b);
     adjoint_batch(angles, order.data() + b, n, n, &fb);
     for (const fdk::SliceRun& r : sl.runs) {
-      // Plain runs: 32-slice bricks and a single accumulation plane; their
-      // flush has no prefetch budget to respect.
-      fdk::TileShape ts =
-          r.mirror ? fdk::tile_shape(g, gc, r, fb.vb, fdk::kBrickZ, fdk::kTileEntryBytes,
-                                     fdk::kPrefetchSlots, direct)
-                   : fdk::tile_shape(g, gc, r, fb.vb, fdk::kPlainBrickZ, fdk::kPlainEntryBytes,
-                                     std::numeric_limits<int32_t>::max(), direct);
+      fdk::TileShape ts = fdk::fp_tile_shape(g, gc, r, fb.vb, direct);
       const int64_t bricks = static_cast<int64_t>(ts.nbx) * ts.nby * ts.nseg;
       if (adjoint_batch(angles, order.data() + b, n, adjoint_chunk(bricks, n), &fb)) ts.span = 0;
       if (int e = fdk::launch_forward_project(gc, r, fb, ts, vol, q, vstride, scale, fixed_sums,

@@ -108,11 +108,13 @@ constexpr int kTileLdsBytes = 36352;    // LDS budget for the adjoint's and the 
 constexpr int kBpTileLdsBytes = 28032;  // and for the five-wave back-projector's (27.4 KB)
 constexpr int kTileEntryBytes = 16;     // (q, dq/du) of a row and of its mirror row
 
+constexpr int kFpWideLdsBytes = 47104;  // for the adjoint's wide tiles: three workgroups a CU
+
 struct TileShape {
   int32_t tu, tv, tvp;   // tile columns, rows, and the (odd) column pitch in entries
   int32_t vc;            // views staged at once; 0 selects the direct variant
   int32_t rstep, rows;   // staging: rows advanced per pass, passes per view
-  int32_t wide;          // back-projector: the four-wave instance with kWidePrefetchSlots
+  int32_t wide;          // the back-projector's four-wave instances; the adjoint's wide kernel
   int32_t span;          // slices whose taps lie in span + 2 consecutive rows, at every column (0: none)
   int32_t np;            // back-projector: slices (pairs) per thread
   int32_t groups;        // back-projector: 256-thread groups per workgroup (0: the general kernel)
@@ -161,6 +163,10 @@ constexpr bool stage_reach_ok(int32_t nu, int32_t nv, int32_t reach) {
 constexpr double kSpanDrift = 0.95;
 // Tile, brick and workgroup of a back-projection launch.
 TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& run,
+                        const ViewBatch& vb, bool direct);
+// Bytes of an adjoint tile's pixel, and its launches.
+constexpr int32_t fp_entry_bytes(bool mirror) { return mirror ? 8 : 4; }
+TileShape fp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& run,
                         const ViewBatch& vb, bool direct);
 // Plain (unmirrored) back-projection runs: 32 slices per brick, the tile
 // holding (q, dq/du) of the main rows only; a prefetch slot holds one row's

@@ -223,7 +223,13 @@ __device__ __forceinline__ void walk_rows(float o, float eps, const float* x, co
   emit(kWalk + 1, c1, m1);
 }
 
-template <bool MIRROR, bool WALK>
+// WIDE: tiles past the other kernels' stages (fp_tile_shape), with the direct
+// kernel's FP64 columns (pixels up to 60 from the origin) and 64-bit sums,
+// whose error is no larger than FP32 sums' (8.1e-7 against 8.4e-7 of FP64 at
+// the size below; 32-bit ones, 30 % faster, have 9.1e-7). What was 8 global
+// atomics a voxel and view, which bound the direct kernel, is one a pixel of
+// the tile: 52 x 75 x 77 from 40 views at 1.33 pixels a voxel 1.69 -> 0.14 ms.
+template <bool MIRROR, bool WALK, bool WIDE>
 __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun& run,
                                               const FpBatch& fb, const TileShape& ts, const float* __restrict__ vol,
                                               float* __restrict__ q, int64_t vstride,
@@ -314,9 +320,9 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
   // 2^kFp64RangeLog2, with half the views per stage (its entries take twice
   // the bytes); FP32 for a brick with non-finite values, a wider range, or
   // when a stage holds a single view.
-  // (With fixed_sums every finite brick takes 32 bits.)
+  // (With fixed_sums every finite brick takes 32 bits, with WIDE 64.)
   const bool wide_range =
-      !fixed_sums && 100u * n_small > static_cast<uint32_t>(kFpWideRangePct) * n_nonzero;
+      WIDE || (!fixed_sums && 100u * n_small > static_cast<uint32_t>(kFpWideRangePct) * n_nonzero);
   const bool fixed64 = nonfinite == 0u && wide_range && ts.vc >= 2 &&
                        __uint_as_float(amax_bits) <=
                            ldexpf(__uint_as_float(amin_bits), kFp64RangeLog2);
@@ -353,7 +359,9 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
     // (main, mirror) entries, and that of plain runs as 64-bit words.)
     if (bc.owner) {
       for (int32_t sl = 0; sl < nvc; ++sl) {
-        const ColumnF32 c = column_f32(bvs[s0 + sl], bc.txf, bc.tyf, kvf);
+        const ColumnF32 c =
+            WIDE ? column_f64(gc, view_geo(gc, vb.sn[s0 + sl], vb.cs[s0 + sl]), bvs[s0 + sl], bc.i, bc.j, bc.kb)
+                 : column_f32(bvs[s0 + sl], bc.txf, bc.tyf, kvf);
         const uint32_t nu = min(c.nu, static_cast<uint32_t>(ts.tu - 1));
         if (!fp32_path) {
           const float km = kw[s0 + sl] * amax_1;
@@ -361,7 +369,7 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
           int e;
           frexpf(km, &e);
           const float du0 = 1.0f - c.du;
-          if (fixed64) {
+          if (WIDE || fixed64) {
             // S = 2^(63 - e), applied to W x (at most M) so that no
             // intermediate overflows.
             const int sh = 63 - e;
@@ -588,7 +596,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WALK ?
 void fp_mirror_kernel(GeoConst gc, SliceRun run, FpBatch fb, TileShape ts,
                       const float* __restrict__ vol, float* __restrict__ q, int64_t vstride,
                       float scale, int fixed_sums) {
-  fp_tiled_body<true, WALK>(gc, run, fb, ts, vol, q, vstride, scale, fixed_sums);
+  fp_tiled_body<true, WALK, false>(gc, run, fb, ts, vol, q, vstride, scale, fixed_sums);
 }
 
 template <bool WALK>
@@ -596,7 +604,15 @@ __global__ __launch_bounds__(kThreads)
 void fp_plain_kernel(GeoConst gc, SliceRun run, FpBatch fb, TileShape ts,
                      const float* __restrict__ vol, float* __restrict__ q, int64_t vstride,
                      float scale, int fixed_sums) {
-  fp_tiled_body<false, WALK>(gc, run, fb, ts, vol, q, vstride, scale, fixed_sums);
+  fp_tiled_body<false, WALK, false>(gc, run, fb, ts, vol, q, vstride, scale, fixed_sums);
+}
+
+template <bool MIRROR>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void fp_wide_kernel(GeoConst gc, SliceRun run, FpBatch fb, TileShape ts,
+                    const float* __restrict__ vol, float* __restrict__ q, int64_t vstride,
+                    float scale, int fixed_sums) {
+  fp_tiled_body<MIRROR, false, true>(gc, run, fb, ts, vol, q, vstride, scale, fixed_sums);
 }
 
 template <bool MIRROR>
@@ -662,24 +678,12 @@ int launch_forward_project(const GeoConst& gc, const SliceRun& run, const FpBatc
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (ts.vc > 0) {
     const dim3 grid(static_cast<uint32_t>(nwg), static_cast<uint32_t>(fb.nchunks));
-    // Adjoint tile: one more column than the back-projection tile, one
-    // 32-bit word per pixel and plane (main, plus mirror for mirrored runs).
-    // The host sizes the back-projection tile at 16 (mirrored) or 8 (plain)
-    // bytes per entry, so at least one view's tile always fits.
-    // The column pitch is padded to 3, 5, 11 or 13 mod 16 words, which
-    // spreads lanes in neighbouring columns and rows over the banks (modelled
-    // clocks per wave instruction: 64-bit 8.2, 8.8 at 25; 32-bit 7.9-8.4,
-    // 11-12 at 1, 9 or 15 mod 16).
-    TileShape tf = ts;
-    while (tf.tvp % 16 != 3 && tf.tvp % 16 != 5 && tf.tvp % 16 != 11 && tf.tvp % 16 != 13) tf.tvp += 2;
-    const int64_t per_view =
-        static_cast<int64_t>(tf.tu + 1) * tf.tvp * sizeof(int) * (run.mirror ? 2 : 1);
-    tf.vc = static_cast<int32_t>(std::min<int64_t>(kMaxStageViews, kTileLdsBytes / per_view));
-    if (tf.vc < 1) return static_cast<int>(hipErrorInvalidValue);
-    const size_t lds = static_cast<size_t>(tf.vc) * per_view;
-    const auto kernel = run.mirror ? (ts.span >= kWalk ? &fp_mirror_kernel<true> : &fp_mirror_kernel<false>)
-                                   : (ts.span >= kWalk ? &fp_plain_kernel<true> : &fp_plain_kernel<false>);
-    hipLaunchKernelGGL(kernel, grid, block, lds, st, gc, run, fb, tf, vol, q, vstride, scale,
+    const size_t lds = static_cast<size_t>(ts.vc) * (ts.tu + 1) * ts.tvp * fp_entry_bytes(run.mirror != 0);
+    const auto kernel =
+        ts.wide ? (run.mirror ? &fp_wide_kernel<true> : &fp_wide_kernel<false>)
+        : run.mirror ? (ts.span >= kWalk ? &fp_mirror_kernel<true> : &fp_mirror_kernel<false>)
+                     : (ts.span >= kWalk ? &fp_plain_kernel<true> : &fp_plain_kernel<false>);
+    hipLaunchKernelGGL(kernel, grid, block, lds, st, gc, run, fb, ts, vol, q, vstride, scale,
                        static_cast<int>(fixed_sums));
   } else {
     const dim3 grid(static_cast<uint32_t>(nwg));

@@ -4,6 +4,7 @@
 // tile-bound test, which checks it against every voxel's taps).
 #include <algorithm>
 #include <cmath>
+#include <limits>
 
 #include "fdk_internal.h"
 
@@ -77,6 +78,32 @@ TileShape tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& 
   const int64_t vc4 = std::min<int64_t>({kBpStageViews, kTileLdsBytes / per_view, wide_slots / ts.rows});
   ts.wide = vc5 < kBpStageViews && vc4 > vc5;
   ts.vc = static_cast<int32_t>(std::max<int64_t>(ts.wide ? vc4 : vc5, 0));
+  return ts;
+}
+
+// Tiles and stages of an adjoint launch (vc = 0: the direct kernel).
+//
+// A tile has one more column than the back-projector's and one 32-bit word a
+// pixel and plane (main, plus mirror for mirrored runs). The column pitch is
+// padded to 3, 5, 11 or 13 mod 16 words, which spreads lanes in neighbouring
+// columns and rows over the banks (modelled clocks per wave instruction:
+// 64-bit 8.2, 8.8 at 25; 32-bit 7.9-8.4, 11-12 at 1, 9 or 15 mod 16). Sized
+// at the back-projector's bytes an entry, twice these, one view's tile always
+// fits. Where that leaves none, or its staging slots too few for a mirrored
+// tile, a tile in up to kFpWideLdsBytes (three workgroups a CU) still takes
+// the adds off the global atomics: the wide kernel.
+TileShape fp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& run,
+                        const ViewBatch& vb, bool direct) {
+  const bool mirror = run.mirror != 0;
+  const int32_t bz = mirror ? kBrickZ : kPlainBrickZ;
+  TileShape ts = tile_shape(g, gc, run, vb, bz, mirror ? kTileEntryBytes : kPlainEntryBytes,
+                            mirror ? kPrefetchSlots : std::numeric_limits<int32_t>::max(), direct);
+  if (direct || ts.rstep == 0) return ts;
+  ts.wide = ts.vc == 0;
+  while (ts.tvp % 16 != 3 && ts.tvp % 16 != 5 && ts.tvp % 16 != 11 && ts.tvp % 16 != 13) ts.tvp += 2;
+  const int64_t per_view = static_cast<int64_t>(ts.tu + 1) * ts.tvp * fp_entry_bytes(mirror);
+  ts.vc = static_cast<int32_t>(std::min<int64_t>(
+      kMaxStageViews, (ts.wide ? kFpWideLdsBytes : kTileLdsBytes) / per_view));
   return ts;
 }
 

@@ -14,7 +14,7 @@
 // Usage: row_walk_check SEED COUNT
 // Prints "<kind> launches=.. walked=.. columns=.. np16=.. np8=.. np4=..
 // groups=.. bad_shape=.. load=.. low=.. high=.. offset=..
-// adj_bricks=.. adj_walked=.. adj_low=.. adj_high=.. adj_over=.. adj_slack=.."
+// adj_bricks=.. adj_walked=.. adj_wide=.. adj_low=.. adj_high=.. adj_over=.. adj_slack=.."
 // (the mean of bound over histogram maximum, in per cent).
 #include <algorithm>
 #include <cinttypes>
@@ -43,7 +43,7 @@ struct SplitMix64 {  // Steele, Lea and Flood (2014)
 struct Stats {
   long launches = 0, walked = 0, columns = 0, np[3] = {0, 0, 0}, groups = 0;
   long bad_shape = 0, load = 0, low = 0, high = 0, offset = 0;
-  long adj_bricks = 0, adj_walked = 0, adj_low = 0, adj_high = 0, adj_over = 0;
+  long adj_bricks = 0, adj_walked = 0, adj_wide = 0, adj_low = 0, adj_high = 0, adj_over = 0;
   double adj_slack = 0.0;  // sum of bound / histogram maximum
 };
 
@@ -138,9 +138,14 @@ void check_adjoint(const fdk_geometry& g, const fdk::GeoConst& gc, const fdk::Sl
   using namespace fdk;
   const bool mirror = run.mirror != 0;
   const int32_t bz = mirror ? kBrickZ : kPlainBrickZ, walk = kBrickZ / 2;
-  const TileShape ts = mirror ? tile_shape(&g, gc, run, vb, bz, kTileEntryBytes, kPrefetchSlots, false)
-                              : tile_shape(&g, gc, run, vb, bz, kPlainEntryBytes, 1 << 30, false);
+  const TileShape ts = fp_tile_shape(&g, gc, run, vb, false);
   if (ts.vc <= 0) return;
+  st->adj_wide += ts.wide;
+  // Twice the bytes a view in the 64-bit sums: they stage vc / 2 views.
+  const int64_t lds = static_cast<int64_t>(ts.vc) * (ts.tu + 1) * ts.tvp * fp_entry_bytes(mirror);
+  if (lds > (ts.wide ? kFpWideLdsBytes : kTileLdsBytes) || ts.vc > kMaxStageViews ||
+      ts.tu + 1 > kBrickThreads || ts.tvp < ts.tv)
+    ++st->bad_shape;
   const float kvf = static_cast<float>(gc.kv);
   for (int n = 0; n < 8; ++n) {
     const int32_t s = rng->irange(0, vb.nviews - 1);
@@ -167,6 +172,9 @@ void check_adjoint(const fdk_geometry& g, const fdk::GeoConst& gc, const fdk::Sl
       for (int32_t i = i_lo; i <= i_hi; ++i) {
         const ColumnF32 c = column_f32(b, static_cast<float>(i - i_lo), static_cast<float>(j - j_lo), kvf);
         hist[std::min<uint32_t>(c.nu, ts.tu - 1) + 1] += slots_at_row(c.dvk, bz);
+        // Highest row of the one-slice-at-a-time kernels (their first is >= 0).
+        if (static_cast<float>(c.nvb) + c.fvb + static_cast<float>(bz - 1) * c.dvk + 1.0f >= static_cast<float>(ts.tv))
+          ++st->adj_high;
         const float down = std::fmin(static_cast<float>(walk - 1) * c.eps, 0.0f);
         for (int32_t k0 = 0; walks && k0 < bz; k0 += walk) {
           const float fl = floorf(fmaf(static_cast<float>(k0), c.eps, c.vl) + down);
@@ -233,10 +241,10 @@ int main(int argc, char** argv) {
   for (int k = 0; k < 2; ++k) {
     const Stats& s = all[k];
     std::printf("%s launches=%ld walked=%ld columns=%ld np16=%ld np8=%ld np4=%ld groups=%ld "
-                "bad_shape=%ld load=%ld low=%ld high=%ld offset=%ld adj_bricks=%ld adj_walked=%ld adj_low=%ld "
+                "bad_shape=%ld load=%ld low=%ld high=%ld offset=%ld adj_bricks=%ld adj_walked=%ld adj_wide=%ld adj_low=%ld "
                 "adj_high=%ld adj_over=%ld adj_slack=%ld\n",
                 names[k], s.launches, s.walked, s.columns, s.np[0], s.np[1], s.np[2], s.groups,
-                s.bad_shape, s.load, s.low, s.high, s.offset, s.adj_bricks, s.adj_walked, s.adj_low, s.adj_high,
+                s.bad_shape, s.load, s.low, s.high, s.offset, s.adj_bricks, s.adj_walked, s.adj_wide, s.adj_low, s.adj_high,
                 s.adj_over, static_cast<long>(100.0 * s.adj_slack / std::max(1l, s.adj_bricks)));
   }
   return 0;

@@ -120,6 +120,37 @@ def test_adjoint_walk_matches_oracle(size, views, cone, slope, off_v):
         assert rel_l2(host(got), 2.0 * ref) <= tol
 
 
+@pytest.mark.parametrize("pixels, cone, off_v", [
+    (1.33, 3.0, 0.0), (2.0, 6.0, 0.0), (2.6, 6.0, 0.0), (2.0, 6.0, 0.27), (3.0, 6.0, 0.27),
+    (5.0, 6.0, 0.0), (5.0, 6.0, 0.27)])
+def test_adjoint_wide_tiles_match_oracle(pixels, cone, off_v):
+    """Several pixels a voxel, wide cones: tiles of the wide kernel, of one and
+    of two stages, and past it. Same tolerance; volumes with a non-finite voxel
+    or with magnitudes too far apart for 64-bit sums give the direct kernel's
+    non-finite pixels and its values."""
+    nx, ny, nz = 33, 45, 38
+    g = synth.Geom(nx=nx, ny=ny, nz=nz, nu=int(50 * pixels), nv=int(46 * pixels), sod=cone * ny,
+                   sdd=2.0 * cone * ny, du=2.0 / pixels, dv=2.0 / pixels, off_u=0.3, off_v=off_v)
+    ang = synth.angles(11, start=0.3)
+    rng = np.random.default_rng(3)
+    x = rng.standard_normal((nz, ny, nx)).astype(np.float32)
+    far = (x * np.exp(rng.uniform(-30.0, 10.0, x.shape))).astype(np.float32)
+    for vol in (x, far):
+        ref = oracle.forward_project(g, ang, vol.astype(np.float64), scale=1.0e4)
+        got = fdk.forward_project(torch.from_numpy(vol).to(DEV), g, ang, scale=1.0e4)
+        err = rel_l2(host(got), ref)
+        print(f"adjoint wide pixels={pixels} off_v={off_v} {err:.2e}", flush=True)
+        assert err <= 1e-5
+    for bad in (np.inf, np.nan):
+        x[5, 7, 9] = bad
+        v = torch.from_numpy(x).to(DEV)
+        got = host(fdk.forward_project(v, g, ang))
+        want = host(fdk.forward_project(v, g, ang, direct=True))
+        fine = np.isfinite(want)
+        assert not fine.all() and np.array_equal(fine, np.isfinite(got))
+        assert rel_l2(got[fine], want[fine]) <= 1e-5
+
+
 @pytest.mark.parametrize("magnitude", [1e-36, 1e-27, 1e36])
 def test_adjoint_at_the_ends_of_the_float_range(magnitude):
     """The sums are scaled to the brick's largest voxel, so volumes near either

@@ -42,6 +42,6 @@ def test_row_walk_stays_inside_the_tile(checker, seed):
         assert s["walked"] >= 500 and s["columns"] >= 500_000, (kind, s)
         assert min(s["np16"], s["np8"], s["np4"], s["groups"]) >= 50, (kind, s)
         # The adjoint: walks in its tile, pixels within the bound, the bound not wide.
-        assert s["adj_walked"] >= 1000 and s["adj_slack"] <= 200, (kind, s)
+        assert s["adj_walked"] >= 1000 and s["adj_wide"] >= 20 and s["adj_slack"] <= 200, (kind, s)
         assert s["adj_low"] == s["adj_high"] == s["adj_over"] == 0, (kind, s)
         assert s["bad_shape"] == s["load"] == s["low"] == s["high"] == s["offset"] == 0, (kind, s)
