@@ -123,10 +123,14 @@ TileShape fp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRu
 //    864 bricks: 306 with one, 380 with two, which no longer fit at once).
 // Tiles of which two do not fit the 35.5 KB of a quarter of a CU's LDS: plain
 // runs take the staged kernel all the same (301 x 277 x 199 at 1.2 pixels a
-// voxel: 2.08 -> 1.72 ms), small mirrored grids bricks of 8 slices (450
-// bricks: 690 us general, 559 at 16 slices, 528 at 8), and large mirrored
-// grids the general kernel (400^3, wide cone: 4.0 ms, staged 4.1 at 16 slices
-// and 4.8 at 8).
+// voxel: 2.08 -> 1.69 ms), small mirrored grids bricks of 8 slices (450
+// bricks: 690 us general, 559 at 16 slices, 528 at 8). Large mirrored grids
+// get a pitch of 3, 7, 9 or 13 mod 16, next to 7 or 9 only, if two tiles then
+// fit (columns five apart may share a bank at 3 and 13; 340 x 347 x 389 from
+// 78 views: 1.37 -> 1.27 ms, 406 x 245 x 313 from 132: 1.71 general, 1.76
+// staged at the wider pitch, 1.57), and else the general kernel (400^3, wide
+// cone: 4.0 ms, staged 4.1; 371 x 412 x 350: 4.62, 5.45, 4.49 with bricks of 8
+// slices, which lose 10 % at 333 x 367 x 311 from 31 views).
 TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& run,
                         const ViewBatch& vb, bool direct) {
   const int32_t entry = run.mirror ? kTileEntryBytes : kPlainEntryBytes;
@@ -157,7 +161,14 @@ TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRu
       if (staged(t) && (bricks(t) <= kCus || (ts.vc != kBpStageViews && np == kMidBrickZ))) ts = t;
     }
   }
-  if (!staged(ts) || (run.mirror && ts.vc != kBpStageViews && !few)) return ts;
+  if (run.mirror && ts.vc != kBpStageViews && !few) {
+    TileShape t = ts;
+    t.tvp = t.tv | 1;
+    while (t.tvp % 16 != 3 && t.tvp % 16 != 7 && t.tvp % 16 != 9 && t.tvp % 16 != 13) t.tvp += 2;
+    if (lds(t, 1) > kTileLdsBytes || !staged(t)) return ts;
+    ts = t;
+  }
+  if (!staged(ts)) return ts;
   ts.groups = bricks(ts) <= kCus ? kMaxGroups : 2 * bricks(ts) <= 3 * kCus ? 2 : 1;
   while (ts.groups > 1 && (ts.groups > vb.nviews || lds(ts, ts.groups) > kGroupLdsBytes))
     ts.groups /= 2;

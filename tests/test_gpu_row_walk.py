@@ -62,6 +62,16 @@ def test_launch_shapes_match_oracle(size, views, slope, off_v):
     assert rel_l2(host(out), base + ref) <= 1e-5
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+def test_narrow_pitch_of_large_grids(dtype):
+    """Mirrored grids beyond the resident bricks with tiles of which two fit a
+    workgroup's share of LDS only at a column pitch of 3 or 13 mod 16."""
+    g = geom((180, 225, 197), 1.0, 0.0, cone=1000.0 / 225)
+    ang = synth.angles(3, start=0.37)
+    qt = torch.from_numpy(synth.random_projections(8, 3, g)).to(DEV, dtype)
+    assert rel_l2(host(fdk.backproject(qt, g, ang)), oracle.backproject(g, ang, host(qt))) <= 1e-5
+
+
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("size", ["tiny", "medium", "large"])
 @pytest.mark.parametrize("off_v", [0.0, 0.27], ids=["mirrored", "plain"])
