@@ -4,8 +4,9 @@
 // kernel is even, so the convolution matrix is symmetric, and the weighting
 // is diagonal.
 //
-// Short rows (and rows too long for the FFT tile) use a direct convolution:
-// one workgroup per row, the weighted row and the kernel taps in LDS.
+// Short rows are multiplied by the convolution's Toeplitz matrix on the matrix
+// units, in FP64. Rows too long for the FFT tile use a direct convolution: one
+// workgroup per row, the weighted row and the kernel taps in LDS.
 //
 // Longer rows use the convolution theorem (Sec. 2.2.3) on the row's first
 // difference and the running sum of the kernel (an identity by summation by
@@ -32,7 +33,7 @@ namespace {
 
 constexpr int kFilterThreads = 256;
 constexpr int kFftMaxLog = 13;             // L <= 8192 complex points (132 KiB of LDS)
-constexpr int kDirectMaxNu = 256;          // below this the direct kernel is cheaper
+constexpr int kMatrixMaxNu = 256;          // up to this the matrix product is cheaper than the FFT
 constexpr int kDirectMaxLds = 8192;        // widest row of the direct kernel (2 x 64 KB of LDS)
 
 // Ramp kernel h(n) at sample pitch tau: Ram-Lak (band-limited ramp) or
@@ -109,6 +110,123 @@ __global__ __launch_bounds__(kFilterThreads) void filter_direct_kernel(
     }
     store_q(qr + a, static_cast<float>(ADJ ? acc * cos_weight_f64(gc, du, dv, sdd, a, b) : acc));
   }
+}
+
+// Short rows (up to kMatrixMaxNu pixels): the direct convolution as a product
+// with the Toeplitz matrix tau h(|a - n|), in the FP64 matrix instructions,
+// which sum as the direct kernel does (one FMA a tap, n upwards). 16 rows a
+// workgroup; its four waves take every fourth tile of 16 output pixels. Taps
+// lie in LDS by a - n, so that a tile of the matrix is 19 of them, rows at a
+// pitch of 2 mod 4 doubles (16 rows on 16 even banks). Bound at 256 pixels by
+// the FP64 rate (320 of 415 us at 131072 rows; 218 at 78.6 TFLOP/s), at 64 by
+// a workgroup's chain of load, weight, product and store. The direct kernel,
+// which read two doubles from LDS a tap and left threads beyond the row idle,
+// took 1480 us there, 2.56 ms instead of 0.67 for 480000 rows of 160 pixels
+// and 30 instead of 15 for 10000 of 100.
+constexpr int kMatrixRows = 16;
+// Below two workgroups a CU the output columns are shared out as well, 64 a
+// workgroup: 1600 rows of 256 pixels 24.8 -> 19.2 us; at the line 45 and 47 us.
+constexpr int64_t kMatrixFewGroups = 2 * kCus;
+using f64x4 = __attribute__((ext_vector_type(4))) double;
+
+constexpr int32_t matrix_pitch(int32_t nu) { return ((nu + 3) & ~3) + 2; }
+constexpr size_t matrix_lds(int32_t nu, int32_t tiles) {
+  return sizeof(double) * (kMatrixRows * matrix_pitch(nu) + ((nu + 3) & ~3) + 64 * tiles);
+}
+
+// Output tiles n0, n0 + 64, ... (TILES of them) of the workgroup's rows.
+template <int TILES, typename Emit>
+__device__ __forceinline__ void matrix_tiles_of(const double* arow, const double* taps, int32_t k4,
+                                                Emit emit) {
+  if constexpr (TILES > 0) {
+    f64x4 acc[TILES];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int32_t k = 0; k < k4; k += 4) {
+      const double a = arow[k];
+#pragma unroll
+      for (int t = 0; t < TILES; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, taps[64 * t - k], acc[t], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) emit(t, acc[t]);
+  }
+}
+
+template <int TILES, typename OutT, bool ADJ>
+__global__ __launch_bounds__(kFilterThreads) void filter_matrix_kernel(
+    GeoConst gc, RowBand rband, double du, double dv, double sdd, double tau, int kind,
+    uint32_t nrows, const float* __restrict__ e, OutT* __restrict__ q) {
+  extern __shared__ double dlds[];
+  __shared__ int64_t qout[kMatrixRows];
+  __shared__ int32_t row_b[kMatrixRows];
+  const int32_t nu = gc.nu, k4 = (nu + 3) & ~3, pitch = matrix_pitch(nu);
+  double* const et = dlds;                          // cosine-weighted rows, zeros from nu
+  double* const taps = dlds + kMatrixRows * pitch;  // tau h(|d|) at d - base + k4 - 1
+  const int32_t base = 64 * TILES * static_cast<int32_t>(blockIdx.y);  // first output pixel
+  const int32_t lane = threadIdx.x % kWaveLanes;
+  const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveLanes);
+  const uint32_t m0 = blockIdx.x * kMatrixRows;
+  const uint32_t band = static_cast<uint32_t>(rband.band);
+#pragma unroll
+  for (int32_t i = 0; i < kMatrixRows / 4; ++i) {
+    const int32_t row = wave + 4 * i;
+    const uint32_t m = m0 + row;
+    const uint32_t s = m / band, r = m - s * band;
+    const bool valid = m < nrows;
+    const int32_t b = static_cast<int32_t>(rband.v0 + r);
+    const float* const er = e + (s * rband.e_stride + static_cast<int64_t>(r) * nu);
+    if (lane == 0) {
+      qout[row] = s * rband.q_stride + static_cast<int64_t>(r) * nu;
+      row_b[row] = b;
+    }
+    for (int32_t a = lane; a < k4; a += kWaveLanes) {
+      const double x = valid && a < nu ? static_cast<double>(er[a]) : 0.0;
+      et[row * pitch + a] = ADJ ? x : x * cos_weight_f64(gc, du, dv, sdd, a, b);
+    }
+  }
+  for (int32_t i = threadIdx.x; i < k4 + 64 * TILES; i += kFilterThreads) {
+    const int32_t d = base + i - (k4 - 1), n = d < 0 ? -d : d;
+    taps[i] = n < nu ? tau * ramp_tap(kind, n, tau) : 0.0;
+  }
+  __syncthreads();
+
+  // Lane l holds row l mod 16 of the 16 x 4 operand and column l mod 16 of the
+  // 4 x 16 one, at depth l / 16; element j of its sums is row 4 j + l / 16.
+  const int32_t col = lane % 16, depth = lane / 16;
+  const double* const arow = et + col * pitch + depth;
+  const double* const btap = taps + (k4 - 1 + 16 * wave + col - depth);
+  auto emit = [&](int t, const f64x4& sum) {
+    const int32_t a = base + 16 * wave + 64 * t + col;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int32_t row = 4 * j + depth;
+      if (a < nu && m0 + row < nrows)
+        store_q(q + qout[row] + a,
+                static_cast<float>(ADJ ? sum[j] * cos_weight_f64(gc, du, dv, sdd, a, row_b[row]) : sum[j]));
+    }
+  };
+  if (base + 16 * wave + 64 * (TILES - 1) < nu)
+    matrix_tiles_of<TILES>(arow, btap, k4, emit);
+  else
+    matrix_tiles_of<TILES - 1>(arow, btap, k4, emit);
+}
+
+template <typename OutT, bool ADJ>
+int launch_matrix(const GeoConst& gc, const RowBand& rb, double du, double dv, double sdd, double tau,
+                  int kind, int64_t nrows, const float* e, OutT* q, hipStream_t st) {
+  const uint32_t groups = static_cast<uint32_t>((nrows + kMatrixRows - 1) / kMatrixRows);
+  const int32_t all = (gc.nu + 63) / 64;  // tiles a wave over the whole row
+  const int32_t tiles = groups < kMatrixFewGroups ? 1 : all;
+  const auto kern = tiles == 1   ? &filter_matrix_kernel<1, OutT, ADJ>
+                    : tiles == 2 ? &filter_matrix_kernel<2, OutT, ADJ>
+                    : tiles == 3 ? &filter_matrix_kernel<3, OutT, ADJ>
+                                 : &filter_matrix_kernel<4, OutT, ADJ>;
+  hipLaunchKernelGGL(kern, dim3(groups, static_cast<uint32_t>(all / tiles)), dim3(kFilterThreads),
+                     matrix_lds(gc.nu, tiles), st, gc, rb, du, dv, sdd, tau, kind,
+                     static_cast<uint32_t>(nrows), e, q);
+  return static_cast<int>(hipGetLastError());
 }
 
 // Lets kernel K use more than the default 64 KB of dynamic LDS on the
@@ -674,13 +792,15 @@ int launch_filter_t(const GeoConst& gc, const RowBand& rb, double du, double dv,
     const int64_t nrows = static_cast<int64_t>(sub.nviews) * sub.band;
     if (nrows == 0) continue;
     int err = 0;
-    if (gc.nu > kDirectMaxNu && logl <= kFftMaxLog) {
+    if (gc.nu > kMatrixMaxNu && logl <= kFftMaxLog) {
       switch (logl) {
         case 10: err = launch_fft<10, OutT, ADJ>(gc, sub, du, dv, sdd, tau, kind, nrows, es, qs, st); break;
         case 11: err = launch_fft<11, OutT, ADJ>(gc, sub, du, dv, sdd, tau, kind, nrows, es, qs, st); break;
         case 12: err = launch_fft<12, OutT, ADJ>(gc, sub, du, dv, sdd, tau, kind, nrows, es, qs, st); break;
         default: err = launch_fft<13, OutT, ADJ>(gc, sub, du, dv, sdd, tau, kind, nrows, es, qs, st); break;
       }
+    } else if (gc.nu <= kMatrixMaxNu) {
+      err = launch_matrix<OutT, ADJ>(gc, sub, du, dv, sdd, tau, kind, nrows, es, qs, st);
     } else {
       const size_t lds = 2 * static_cast<size_t>(gc.nu) * sizeof(double);
       if (lds > 65536) {
