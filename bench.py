@@ -61,29 +61,29 @@ N_CU, CLOCK_HZ, VALU_LANES_PER_CLK = 256, 2.4e9, 128
 LDS_BYTES_PER_CLK = 222.6
 LDS_ATOMIC64_BYTES_PER_CLK = 79.6
 HBM_PEAK = 8.0e12
-# VALU work per voxel-view update of the mirrored, difference-staged scheme:
-# per voxel pair v (1 FMA), truncation, fraction and tap address (3 half
-# rate, shared); per voxel two u-interpolations (1 FMA each on the staged
-# difference), one v-interpolation (2) and the weighted accumulate (1):
-# (1 + 2 * 3 + 2 * 5) / 2 = 8.5 full-rate equivalents.
-VALU_OPS_PER_UPDATE = 8.5
-LDS_BYTES_PER_UPDATE = 16.0  # 4 FP32 taps (value and u-difference of two rows)
-# The adjoint's scheme (fixed-point tile, a row's and its mirror row's sums
-# in one 64-bit word), in full-rate equivalents: per voxel W S x (1), the
-# row split (2), four tap weights (4) and four round-to-fixed conversions
-# (half rate: 8) -> 15; per voxel pair v (1), truncation, fraction and
-# address (half rate: 6) -> 7, and for each of the four 64-bit adds the sign
-# carry of the low half (a shift, half rate, and an add: 3) -> 12; per
-# update (2 * 15 + 7 + 12) / 2 = 24.5, and two 8-byte LDS read-modify-writes
-# (16 bytes).
-ADJ_VALU_OPS_PER_UPDATE = 24.5
-ADJ_LDS_BYTES_PER_UPDATE = 16.0
-TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "bp_tiled_mirror_kernel_bp2048_traffic.json")
+# VALU work per voxel-view update of the mirrored row walk over 8 slices: of
+# its 10 rows two u-interpolations each (1 FMA on the staged difference) and
+# two differences to the next row, 38 per 8 voxel pairs; per pair its offset
+# (1 FMA), two clamps, and for the voxel and its mirror two sample FMAs and the
+# weighted accumulate (6): (38 / 8 + 9) / 2 = 6.875 full-rate operations.
+VALU_OPS_PER_UPDATE = 6.875
+LDS_BYTES_PER_UPDATE = 10.0  # 10 rows of 16 bytes (value and u-difference, main and mirror) per 8 pairs
+# The adjoint's row walk (fixed-point tile, a row's and its mirror row's sums
+# in one 64-bit word), in full-rate equivalents: per voxel pair two clamped
+# offsets, two weights, and for the voxel and its mirror three products -> 10;
+# of 10 rows per 8 pairs two pixel columns each, with two products, two
+# round-to-fixed conversions (half rate: 4) and the sign carry of the low half
+# (a shift, half rate, and an add: 3) -> 18 a row; per update
+# (10 + 180 / 8) / 2 = 16.25, and 20 8-byte LDS read-modify-writes per 16
+# updates (10 bytes).
+ADJ_VALU_OPS_PER_UPDATE = 16.25
+ADJ_LDS_BYTES_PER_UPDATE = 10.0
+TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "bp_staged_kernel_bp2048_traffic.json")
 # Most views per launch of the library's back-projector and adjoint (the
 # volume is read, and written, once per launch); a call's views are split
 # evenly over the fewest launches.
 BP_VIEWS_PER_LAUNCH = 96
-ADJ_VIEWS_PER_LAUNCH = 64
+ADJ_VIEWS_PER_LAUNCH = 96
 # Slab workload: views are filtered in 16-view chunks; six contiguous chunks
 # make one back-projection launch.
 SLAB_VIEWS_PER_LAUNCH = 96
@@ -516,7 +516,7 @@ def main_slab(args):
         "pipeline_gups": round(gups(updates, wall_ms / 1e3), 2),
         "pipeline_ms_per_step": round(wall_ms, 2),
         "roofline": roofline_of(bp_ms, launches, updates, g, cfg["np"] / launches, 2.0,
-                                "bp_tiled_mirror_kernel<f16_t>", None),
+                                "bp_staged_kernel<f16_t>", None),
         "cpu_baseline": None,
     }
     print(json.dumps(out), flush=True)
@@ -630,7 +630,7 @@ def main():
             result_extra[f"{name}_ms_per_step"] = round(ms16, 2)
             result_extra[f"{name}_roofline"] = {
                 k: v for k, v in roofline_of(ms16, launches, updates, g, bp_vpl, 2.0,
-                                             f"bp_tiled_mirror_kernel<{name}_t>", None).items()
+                                             f"bp_staged_kernel<{name}_t>", None).items()
                 if k not in ("traffic", "traffic_unit", "hbm_achieved_GBps",
                              "traffic_over_algorithmic")}
             if not args.no_cpu_baseline:
@@ -679,7 +679,7 @@ def main():
         result_extra["adjoint_roofline"] = {
             k: v for k, v in roofline_of(msa, math.ceil(nv_adj / ADJ_VIEWS_PER_LAUNCH), ua, g,
                                          ADJ_VIEWS_PER_LAUNCH, 4.0,
-                                         "fp_tiled_kernel<true>", None,
+                                         "fp_mirror_kernel<true>", None,
                                          valu_ops=ADJ_VALU_OPS_PER_UPDATE,
                                          lds_bytes=ADJ_LDS_BYTES_PER_UPDATE,
                                          lds_rate=LDS_ATOMIC64_BYTES_PER_CLK).items()
@@ -691,7 +691,7 @@ def main():
     # ---- roofline of the dominant kernel (the back-projection launches) ----
     traffic, valu_insts = profiled_counters(args.workload)
     roofline = roofline_of(ms32, launches, updates, g, bp_vpl, 4.0,
-                           "bp_tiled_mirror_kernel<float>",
+                           "bp_staged_kernel<float>",
                            traffic, valu_insts)
 
     if not args.no_sirt and args.workload == "bp2048":
