@@ -166,11 +166,18 @@ bool adjoint_batch(const double* angles, const int32_t* order, int32_t n, int32_
 // kFpChunkViews views each, since every chunk reads the brick again and sets
 // it up. (128^3 from 90 views and 256^3 from 360: 1280 to 8192 workgroups
 // measure within 4 %, and 16 views a chunk cost 64^3 from 64 views 40 %.)
+// Where that leaves fewer than two workgroups a CU, fewer views, two at
+// least: a chunk's views come one after the other (48^3 from 30 views 29.7 ->
+// 19.0 us, 64^3 from 64 29.0 -> 24.9, 60 x 70 x 80 from 16 26.9 -> 18.0;
+// shorter chunks on larger grids lose: 128^3 from 20 views, 768 workgroups of
+// eight views, 44 us, 1280 of four 53).
 constexpr int64_t kFpGrid = 4096;
-constexpr int32_t kFpChunkViews = 8;
+constexpr int64_t kFpChunkViews = 8;
 int32_t adjoint_chunk(int64_t bricks, int32_t nviews) {
   const int64_t chunks = std::max<int64_t>(1, (kFpGrid + bricks - 1) / bricks);
-  return std::max<int32_t>(kFpChunkViews, static_cast<int32_t>((nviews + chunks - 1) / chunks));
+  const int64_t least =
+      std::min(kFpChunkViews, std::max<int64_t>(fdk::kFpLeastViews, bricks * nviews / (2 * fdk::kCus)));
+  return static_cast<int32_t>(std::max(least, (nviews + chunks - 1) / chunks));
 }
 
 struct Slab {

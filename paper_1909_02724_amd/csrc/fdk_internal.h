@@ -71,7 +71,8 @@ struct ViewBatch {
 // rays run closer to y than to x if across[c] is 0, else closer to x: groups
 // of 16 threads then run along x or y, across the rays. rot_a, rot_b: see
 // slot_rotation (fp.hip).
-constexpr int kMaxChunks = 32;
+constexpr int kFpLeastViews = 2;  // of a chunk, but for the last of a direction
+constexpr int kMaxChunks = kMaxViewsPerLaunch / kFpLeastViews + 2;  // one direction after the other
 struct FpBatch {
   ViewBatch vb;
   int32_t idx[kMaxViewsPerLaunch];

@@ -130,6 +130,18 @@ def test_adjoint_walk_matches_oracle(size, views, cone, slope, off_v):
         assert rel_l2(host(got), 2.0 * ref) <= tol
 
 
+@pytest.mark.parametrize("off_v", [0.0, 0.27], ids=["mirrored", "plain"])
+@pytest.mark.parametrize("views", [1, 2, 3, 5, 62, 63, 96, 97, 191])
+def test_adjoint_short_chunks_match_oracle(views, off_v):
+    """Few bricks: chunks of two views, up to 49 of them in a launch, the last
+    of a direction shorter. Tolerance as above."""
+    g = geom((17, 20, 18), 1.0, off_v)
+    ang = synth.angles(views, start=0.2)
+    x = np.random.default_rng(views).standard_normal((g.nz, g.ny, g.nx)).astype(np.float32)
+    got = fdk.forward_project(torch.from_numpy(x).to(DEV), g, ang, scale=1.0e4)
+    assert rel_l2(host(got), oracle.forward_project(g, ang, x.astype(np.float64), scale=1.0e4)) <= 1e-5
+
+
 @pytest.mark.parametrize("pixels, cone, off_v", [
     (1.33, 3.0, 0.0), (2.0, 6.0, 0.0), (2.6, 6.0, 0.0), (2.0, 6.0, 0.27), (3.0, 6.0, 0.27),
     (5.0, 6.0, 0.0), (5.0, 6.0, 0.27)])
