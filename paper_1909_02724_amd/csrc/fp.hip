@@ -2,7 +2,7 @@
 // voxel scatters scale * W * w_tap * vol into its four taps, with exactly the
 // coordinates and weights of the matching back-projection variant (same
 // brick setup, brick.h; FP32 columns for the tiled variant, FP64 columns for
-// the direct one), so each is the transpose of its back-projector up to
+// wide tiles and the direct one), so each is the transpose of its back-projector up to
 // rounding.
 #include <hip/hip_runtime.h>
 

@@ -19,7 +19,7 @@ HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 
 
 @pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def walk_exe(tmp_path_factory):
     exe = tmp_path_factory.mktemp("walk") / "row_walk_check"
     cmd = [HIPCC, "-std=c++17", "-O2", "--offload-arch=gfx950", "--cuda-host-only",
            "-x", "hip", os.path.join(ROOT, "tests", "row_walk_check.cpp"),
@@ -31,8 +31,8 @@ def checker(tmp_path_factory):
 
 
 @pytest.mark.parametrize("seed", [5, 20250311])
-def test_row_walk_stays_inside_the_tile(checker, seed):
-    out = subprocess.run([str(checker), str(seed), "4000"], capture_output=True, text=True,
+def test_row_walk_stays_inside_the_tile(walk_exe, seed):
+    out = subprocess.run([str(walk_exe), str(seed), "4000"], capture_output=True, text=True,
                          check=True).stdout
     print(out)
     for line in out.splitlines():
