@@ -149,39 +149,35 @@ __device__ __forceinline__ void write_back(const GeoConst& gc, const SliceRun& r
 // their mirrors). Along a column v advances by dv/dk = 1 + eps a slice, and
 // the detector and voxel pitches usually make eps small, so the taps of SPAN
 // consecutive slices lie in SPAN + 2 consecutive rows whenever
-// (SPAN - 1) |eps| < 1: slice j of the block has v = n + j + o_j with
-// o_j = o_0 + j eps in [0, 2), n fixed for the block. Each row is read and
+// (SPAN - 1) |eps| < 1: slice j of the block has v = n + j + 1 + x_j with
+// x_j = x_0 + j eps in (-1, 1), n fixed for the block. Each row is read and
 // interpolated in u once, at a constant offset from the block's first row,
-// instead of two rows a voxel at computed addresses; the bilinear sample is
-//   R_j + clamp(o_j) (R_j+1 - R_j) + clamp(o_j - 1) (R_j+2 - R_j+1)
-// (clamp to [0, 1], an output modifier), the same piecewise linear function.
-// A voxel pair then costs 12.75 full-rate VALU instructions and 20 bytes of
-// LDS reads at SPAN = 8, against 11 full-rate and 3 half-rate ones and 32
-// bytes with pair_column. What bounds it is VALU issue (278 instructions per
-// wave and view, staging and column setup included: 73 % of the issue slots
-// at the full rate) at a clock that the power limit holds to about 1.95 GHz.
-// 512^3 from 512 views: 14.8 -> 12.7 ms together with the staged body; the
-// same walk in the general body's staging gave 14.2.
-// A row outside the voxel's two taps enters with weight zero, so a NaN or an
-// infinity there spreads one voxel too far: a brick with a sum that is not
-// finite is redone with pair_column. Rows are read kSpanAhead rows early
-// (1, 2 and 3 measure within 1 %; 3 spills in 16-bit instances).
+// instead of two rows a voxel at computed addresses. The sample is
+//   R_j+1 + |x_j| (S - R_j+1),  S = R_j if x_j < 0, else R_j+2.
+// The row that is no tap is selected away, so that nothing of it enters, be it
+// a NaN or the rounding of a pixel far larger than its neighbours. (Summed at a
+// weight of zero, as clamp(o) and clamp(o - 1) times the rows' differences, it
+// left 2^-24 of itself behind, and bricks with a NaN had to be computed twice.)
+// A slice on a row has it as its R_j+1, n being below: its sample is that row's.
+// A voxel pair then costs 12.5 full-rate VALU instructions and 20 bytes of LDS
+// reads at SPAN = 8, against 11 full-rate and 3 half-rate ones and 32
+// bytes with pair_column. What bounds it is VALU issue
+// at a clock that the power limit holds to about 1.95 GHz. Rows are read
+// kSpanAhead rows early (1, 2 and 3 measure within 1 %; 3 spills in 16-bit
+// instances).
 constexpr int kSpanAhead = 2;
 template <bool MIRROR, int SPAN, int NP>
 __device__ __forceinline__ void span_column(const std::conditional_t<MIRROR, float4, float2>* col,
                                             const ColumnF32& c, float* acc, float* accm) {
   using Entry = std::conditional_t<MIRROR, float4, float2>;
   constexpr int BLOCKS = (MIRROR ? NP : 2 * NP) / SPAN, ROWS = SPAN + 2;
-  // First row of each block (the smallest v of its slices, less j), and o_0.
-  const Entry* first[BLOCKS];
-  float o0[BLOCKS];
-  const float down = fminf(static_cast<float>(SPAN - 1) * c.eps, 0.0f);
+  const Entry* first[BLOCKS];  // first row of each block, and x of its first slice
+  float x0[BLOCKS];
 #pragma unroll
   for (int b = 0; b < BLOCKS; ++b) {
-    const float o = b ? fmaf(static_cast<float>(b * SPAN), c.eps, c.vl) : c.vl;
-    const float n = floorf(o + down);
-    o0[b] = o - n;
-    first[b] = col + (b * SPAN + static_cast<int32_t>(n));
+    const WalkStart start = walk_start(c, b * SPAN, SPAN);
+    x0[b] = start.x;
+    first[b] = col + start.row;
   }
   // Rows are read kSpanAhead rows before their use, across blocks; the
   // fences keep the compiler from issuing them all at once, which spills.
@@ -202,30 +198,27 @@ __device__ __forceinline__ void span_column(const std::conditional_t<MIRROR, flo
       if constexpr (MIRROR) return fmaf(c.du, raw[b * ROWS + r].w, raw[b * ROWS + r].z);
       return 0.0f;
     };
-    const float o1 = o0[b] - 1.0f;
-    float r0 = main_u(0), r1 = main_u(1), d0 = r1 - r0;
-    float m0 = mirror_u(0), m1 = mirror_u(1), e0 = m1 - m0;
+    float r0 = main_u(0), r1 = main_u(1);
+    float m0 = mirror_u(0), m1 = mirror_u(1);
 #pragma unroll
     for (int j = 0; j < SPAN; ++j) {
       // The rows of the next step: at a block's end, the first three of the next.
       const int next = b * ROWS + j + 2 + (j + 1 < SPAN ? 0 : 2);
       read_to(next + kSpanAhead);
-      const float fj = static_cast<float>(j);
-      const float a = __builtin_amdgcn_fmed3f(fmaf(fj, c.eps, o0[b]), 0.0f, 1.0f);
-      const float bb = __builtin_amdgcn_fmed3f(fmaf(fj, c.eps, o1), 0.0f, 1.0f);
-      const float r2 = main_u(j + 2), d1 = r2 - r1;
+      const float x = fmaf(static_cast<float>(j), c.eps, x0[b]);
+      const bool below = x < 0.0f;
+      const float far = fabsf(x);
+      const float r2 = main_u(j + 2);
       const int t = b * SPAN + j;
       float* const s = t < NP ? acc + t : accm + (t - NP);
-      *s = fmaf(c.w, fmaf(bb, d1, fmaf(a, d0, r0)), *s);
+      *s = fmaf(c.w, fmaf(far, (below ? r0 : r2) - r1, r1), *s);
       r0 = r1;
       r1 = r2;
-      d0 = d1;
       if constexpr (MIRROR) {
-        const float m2 = mirror_u(j + 2), e1 = m2 - m1;
-        accm[t] = fmaf(c.w, fmaf(bb, e1, fmaf(a, e0, m0)), accm[t]);
+        const float m2 = mirror_u(j + 2);
+        accm[t] = fmaf(c.w, fmaf(far, (below ? m0 : m2) - m1, m1), accm[t]);
         m0 = m1;
         m1 = m2;
-        e0 = e1;
       }
     }
   }
@@ -293,15 +286,16 @@ __device__ __forceinline__ void pair_column(const std::conditional_t<MIRROR, flo
           }
 }
 
-template <typename T, bool MIRROR, bool TILED, bool WIDE = false, int NP = kBrickZ>
+template <typename T, bool MIRROR, bool TILED, bool WIDE = false>
 __device__ __forceinline__ void bp_brick_body(const GeoConst& gc, const SliceRun& run,
                                               const ViewBatch& vb, const TileShape& ts,
                                               const T* __restrict__ q, int64_t vstride,
                                               float* __restrict__ vol, float scale,
-                                              int accumulate, float4* tile, BrickView* bvs,
-                                              int32_t tid, bool writer) {
+                                              int accumulate, float4* tile, BrickView* bvs) {
+  const int32_t tid = threadIdx.x;
   const BpColumn bc = bp_column<MIRROR && TILED>(gc, ts, tid);
   const float txf = bc.txf, tyf = bc.tyf;
+  constexpr int NP = kBrickZ;
   // Mirrored runs: NP (16) slices and their mirrors per thread, tile entries
   // (q, dq, qm, dqm). Plain runs: 2 NP slices per thread (the second NP in the
   // registers the mirrors would use), entries (q, dq).
@@ -509,7 +503,7 @@ __device__ __forceinline__ void bp_brick_body(const GeoConst& gc, const SliceRun
     }
   }
 
-  if (writer) write_back<MIRROR, NP>(gc, run, bc, t0, acc, accm, vol, scale, accumulate);
+  write_back<MIRROR, NP>(gc, run, bc, t0, acc, accm, vol, scale, accumulate);
 }
 
 // Staged body. Two tiles per group of 256 threads, used in turn: a view's tile
@@ -522,19 +516,16 @@ __device__ __forceinline__ void bp_brick_body(const GeoConst& gc, const SliceRun
 // without staging, 6.2 without the column sums.)
 // With GROUPS, blockDim.x / 256 groups share the workgroup's brick, each
 // taking every so many views; their sums meet in LDS in a fixed order at the
-// end. Returns false, nothing written, when a row-walk sum is not finite.
+// end.
 template <typename T, bool MIRROR, int SPAN, int NP, int ROWS, bool EXACT, bool GROUPS>
-__device__ __forceinline__ bool bp_staged_body(const GeoConst& gc, const SliceRun& run,
+__device__ __forceinline__ void bp_staged_body(const GeoConst& gc, const SliceRun& run,
                                              const ViewBatch& vb, const TileShape& ts,
                                              const T* __restrict__ q, int64_t vstride,
                                              float* __restrict__ vol, float scale, int accumulate,
-                                             float4* tile, BrickView* bvs, int32_t* nonfinite) {
+                                             float4* tile, BrickView* bvs) {
   constexpr int BZ = MIRROR ? NP : 2 * NP;
   using Entry = std::conditional_t<MIRROR, float4, float2>;
-  // Opaque to the compiler, which would otherwise keep per-thread values of
-  // this body in registers for the general one that may follow it.
-  int32_t all = threadIdx.x;
-  asm volatile("" : "+v"(all));
+  const int32_t all = threadIdx.x;
   const int32_t tid = all & (kThreads - 1);
   const int32_t groups = GROUPS ? static_cast<int32_t>(blockDim.x) / kThreads : 1;
   const int32_t group = GROUPS ? __builtin_amdgcn_readfirstlane(all / kThreads) : 0;
@@ -543,7 +534,6 @@ __device__ __forceinline__ bool bp_staged_body(const GeoConst& gc, const SliceRu
   const int32_t kb = run.k_first + t0;
   const float kvf = static_cast<float>(gc.kv);
 
-  if (all == 0) *nonfinite = 0;
   if (all < vb.nviews)
     bvs[all] = brick_setup(gc, view_geo(gc, vb.sn[all], vb.cs[all]), bc.i_lo, bc.i_hi, bc.j_lo,
                            bc.j_hi, kb, ts.tu, ts.tv, BZ, MIRROR);
@@ -673,16 +663,7 @@ __device__ __forceinline__ bool bp_staged_body(const GeoConst& gc, const SliceRu
       }
     }
   }
-  if constexpr (SPAN > 0) {
-    float zero = 0.0f;  // stays so unless a sum is a NaN or an infinity
-#pragma unroll
-    for (int t = 0; t < NP; ++t) zero = fmaf(acc[t], 0.0f, fmaf(accm[t], 0.0f, zero));
-    if (group == 0 && zero != 0.0f) *nonfinite = 1;
-    __syncthreads();
-    if (*nonfinite) return false;
-  }
   if (group == 0) write_back<MIRROR, NP>(gc, run, bc, t0, acc, accm, vol, scale, accumulate);
-  return true;
 }
 
 // The general tiled variants run five 256-thread workgroups per CU (five
@@ -697,8 +678,7 @@ void bp_tiled_kernel(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,
                      float scale, int accumulate) {
   extern __shared__ float4 tile[];
   __shared__ BrickView bvs[kMaxViewsPerLaunch];
-  bp_brick_body<T, MIRROR, true>(gc, run, vb, ts, q, vstride, vol, scale, accumulate, tile, bvs,
-                                 static_cast<int32_t>(threadIdx.x), true);
+  bp_brick_body<T, MIRROR, true>(gc, run, vb, ts, q, vstride, vol, scale, accumulate, tile, bvs);
 }
 
 template <typename T, bool MIRROR>
@@ -709,7 +689,7 @@ void bp_tiled_wide_kernel(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,
   extern __shared__ float4 tile[];
   __shared__ BrickView bvs[kMaxViewsPerLaunch];
   bp_brick_body<T, MIRROR, true, true>(gc, run, vb, ts, q, vstride, vol, scale, accumulate, tile,
-                                       bvs, static_cast<int32_t>(threadIdx.x), true);
+                                       bvs);
 }
 
 // Row-walk kernels: the five-wave instance for tiles of kSpanRows passes, and
@@ -722,15 +702,8 @@ void bp_staged_kernel(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,
                     int accumulate) {
   extern __shared__ float4 tile[];
   __shared__ BrickView bvs[kMaxViewsPerLaunch];
-  __shared__ int32_t nonfinite;
-  if (bp_staged_body<T, MIRROR, SPAN, kBrickZ, stage_passes(MIRROR, 0), true, false>(
-          gc, run, vb, ts, q, vstride, vol, scale, accumulate, tile, bvs, &nonfinite))
-    return;
-  if constexpr (SPAN > 0) {
-    __syncthreads();  // the brick's setup is rewritten
-    bp_brick_body<T, MIRROR, true>(gc, run, vb, ts, q, vstride, vol, scale, accumulate, tile, bvs,
-                                   static_cast<int32_t>(threadIdx.x), true);
-  }
+  bp_staged_body<T, MIRROR, SPAN, kBrickZ, stage_passes(MIRROR, 0), true, false>(
+      gc, run, vb, ts, q, vstride, vol, scale, accumulate, tile, bvs);
 }
 
 template <typename T, bool MIRROR, int SPAN, int NP>
@@ -740,17 +713,8 @@ void bp_groups_kernel(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,
                            float scale, int accumulate) {
   extern __shared__ float4 tile[];
   __shared__ BrickView bvs[kMaxViewsPerLaunch];
-  __shared__ int32_t nonfinite;
-  if (bp_staged_body<T, MIRROR, SPAN, NP, stage_passes(MIRROR, NP), false, true>(
-          gc, run, vb, ts, q, vstride, vol, scale, accumulate, tile, bvs, &nonfinite))
-    return;
-  if constexpr (SPAN > 0) {
-    __syncthreads();
-    // Every group redoes the whole brick on the same tiles, and one writes it.
-    bp_brick_body<T, MIRROR, true, true, NP>(
-        gc, run, vb, ts, q, vstride, vol, scale, accumulate, tile, bvs,
-        static_cast<int32_t>(threadIdx.x) & (kThreads - 1), threadIdx.x < kThreads);
-  }
+  bp_staged_body<T, MIRROR, SPAN, NP, stage_passes(MIRROR, NP), false, true>(
+      gc, run, vb, ts, q, vstride, vol, scale, accumulate, tile, bvs);
 }
 
 template <typename T, bool MIRROR>
@@ -762,7 +726,7 @@ __global__ __launch_bounds__(kThreads) void bp_direct_kernel(GeoConst gc, SliceR
                                                              int accumulate) {
   __shared__ BrickView bvs[kMaxViewsPerLaunch];
   bp_brick_body<T, MIRROR, false>(gc, run, vb, ts, q, vstride, vol, scale, accumulate, nullptr,
-                                  bvs, static_cast<int32_t>(threadIdx.x), true);
+                                  bvs);
 }
 
 // Kernel of a launch.

@@ -159,6 +159,19 @@ __host__ __device__ __forceinline__ ColumnF32 column_f32(const BrickView& b, flo
   return c;
 }
 
+// Row walk of slices [k0, k0 + span) of a column: the first of its rows, the
+// one above the smallest v less the slice's place (a row above one that v lies
+// on), and the first slice's v against the row after.
+struct WalkStart {
+  int32_t row;
+  float x;
+};
+__host__ __device__ __forceinline__ WalkStart walk_start(const ColumnF32& c, int32_t k0, int32_t span) {
+  const float o = k0 ? fmaf(static_cast<float>(k0), c.eps, c.vl) : c.vl;
+  const float next = ceilf(o + fminf(static_cast<float>(span - 1) * c.eps, 0.0f));
+  return WalkStart{k0 - 1 + static_cast<int32_t>(next), o - next};
+}
+
 // The same quantities computed per column in FP64 (direct variant: it runs
 // when footprints are too large for LDS, i.e. at strong magnification,
 // where brick-relative FP32 offsets would span hundreds of pixels).
