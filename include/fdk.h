@@ -182,8 +182,10 @@ FDK_API fdk_status fdk_backproject(const fdk_geometry* g, int32_t view0, int32_t
  * 2^-63 K M per contribution: a voxel 2^-40 of the largest reaches a pixel
  * through a full-weight tap at about FP32 precision of its own size), and a
  * brick holding NaN or infinity, or spanning more than 2^40, sums in FP32
- * (unless FDK_FIXED_SUMS, which keeps every finite brick in 32 bits, but for
- * footprints past the 32-bit kernels' tiles, which sum in 64). The workgroups' sums
+ * (unless FDK_FIXED_SUMS, which keeps every finite brick in 32 bits).
+ * Footprints past the 32-bit kernels' tiles sum in 64 bits by the same rules
+ * (with FDK_FIXED_SUMS every finite brick); the direct variant, and footprints
+ * past those tiles too, add every tap in FP32. The workgroups' sums
  * meet in FP32 atomics, so the last bits vary from run to run.
  * Errors: as fdk_backproject. */
 FDK_API fdk_status fdk_forward_project(const fdk_geometry* g, int32_t view0, int32_t nviews,

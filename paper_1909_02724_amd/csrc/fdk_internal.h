@@ -109,7 +109,10 @@ constexpr int kTileLdsBytes = 36352;    // LDS budget for the adjoint's and the 
 constexpr int kBpTileLdsBytes = 28032;  // and for the five-wave back-projector's (27.4 KB)
 constexpr int kTileEntryBytes = 16;     // (q, dq/du) of a row and of its mirror row
 
-constexpr int kFpWideLdsBytes = 47104;  // for the adjoint's wide tiles: three workgroups a CU
+// For the adjoint's wide tiles, of 64-bit sums: three workgroups a CU, or one
+// for a single view's tile past that.
+constexpr int kFpWideLdsBytes = 47104;
+constexpr int kFpWideMostLdsBytes = 2 * kFpWideLdsBytes;
 
 struct TileShape {
   int32_t tu, tv, tvp;   // tile columns, rows, and the (odd) column pitch in entries
@@ -165,8 +168,12 @@ constexpr double kSpanDrift = 0.95;
 // Tile, brick and workgroup of a back-projection launch.
 TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& run,
                         const ViewBatch& vb, bool direct);
-// Bytes of an adjoint tile's pixel, and its launches.
+// Bytes of an adjoint tile's pixel in 32-bit sums (in 64-bit ones twice as many),
+// a launch's dynamic LDS, and its launches.
 constexpr int32_t fp_entry_bytes(bool mirror) { return mirror ? 8 : 4; }
+constexpr int32_t fp_lds_bytes(const TileShape& ts, bool mirror) {
+  return ts.vc * (ts.tu + 1) * ts.tvp * fp_entry_bytes(mirror) * (ts.wide ? 2 : 1);
+}
 TileShape fp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& run,
                         const ViewBatch& vb, bool direct);
 // Plain (unmirrored) back-projection runs: 32 slices per brick, the tile

@@ -95,7 +95,9 @@ __device__ __forceinline__ void load_voxels(const GeoConst& gc, const SliceRun& 
 // Two kinds take FP32 atomics (float tile, planar layout) instead:
 //  - a brick with a NaN or an infinity, which integers cannot carry;
 //  - a wide-range brick spanning more than 2^40, or one whose launch stages
-//    a single view (its 64-bit tile would not fit).
+//    a single view in 32 bits (its 64-bit tile would not fit).
+// The wide kernel's tiles are sized for 64-bit sums and take them for every
+// finite brick up to that range (with FDK_FIXED_SUMS, of any range).
 // The FP32 path is slow (a workgroup on it can take longer than the rest of
 // its launch), so it is kept for what fixed point cannot represent.
 // On the FP32 path each pixel's sum carries FP32 rounding relative to its
@@ -319,15 +321,17 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
   // point for a wide-range brick whose non-zero magnitudes span at most
   // 2^kFp64RangeLog2, with half the views per stage (its entries take twice
   // the bytes); FP32 for a brick with non-finite values, a wider range, or
-  // when a stage holds a single view.
-  // (With fixed_sums every finite brick takes 32 bits, with WIDE 64.)
+  // when a stage holds a single view in 32 bits.
+  // With fixed_sums every finite brick takes 32 bits. WIDE tiles hold 64-bit
+  // sums of ts.vc views, and take them with fixed_sums whatever the range.
   const bool wide_range =
       WIDE || (!fixed_sums && 100u * n_small > static_cast<uint32_t>(kFpWideRangePct) * n_nonzero);
-  const bool fixed64 = nonfinite == 0u && wide_range && ts.vc >= 2 &&
-                       __uint_as_float(amax_bits) <=
-                           ldexpf(__uint_as_float(amin_bits), kFp64RangeLog2);
+  const bool fixed64 = nonfinite == 0u && wide_range && (WIDE || ts.vc >= 2) &&
+                       ((WIDE && fixed_sums) ||
+                        __uint_as_float(amax_bits) <=
+                            ldexpf(__uint_as_float(amin_bits), kFp64RangeLog2));
   const bool fp32_path = nonfinite != 0u || (wide_range && !fixed64);
-  const int32_t vstep = fixed64 ? ts.vc / 2 : ts.vc;
+  const int32_t vstep = fixed64 && !WIDE ? ts.vc / 2 : ts.vc;
 
   // Fixed point: the voxels are scaled by a power of two to magnitudes below
   // 1, so that neither their sums nor the scale of the sums leave FP32's
@@ -346,7 +350,7 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
   const int32_t rstep = kThreads / tuf;
   const int32_t sr = tid / tuf, sc = tid - sr * tuf;
   // Tiles start at zero; the flush leaves them so for the next stage.
-  for (int32_t e = tid; e < (MIRROR ? 2 : 1) * ts.vc * slot; e += kThreads) atile[e] = 0;
+  for (int32_t e = tid; e < (MIRROR ? 2 : 1) * (WIDE ? 2 : 1) * ts.vc * slot; e += kThreads) atile[e] = 0;
   __syncthreads();
   int* const mtile = atile + ts.vc * slot;
   for (int32_t s0 = v_lo; s0 < v_hi; s0 += vstep) {
@@ -678,11 +682,17 @@ int launch_forward_project(const GeoConst& gc, const SliceRun& run, const FpBatc
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (ts.vc > 0) {
     const dim3 grid(static_cast<uint32_t>(nwg), static_cast<uint32_t>(fb.nchunks));
-    const size_t lds = static_cast<size_t>(ts.vc) * (ts.tu + 1) * ts.tvp * fp_entry_bytes(run.mirror != 0);
+    const int32_t lds = fp_lds_bytes(ts, run.mirror != 0);
     const auto kernel =
         ts.wide ? (run.mirror ? &fp_wide_kernel<true> : &fp_wide_kernel<false>)
         : run.mirror ? (ts.span >= kWalk ? &fp_mirror_kernel<true> : &fp_mirror_kernel<false>)
                      : (ts.span >= kWalk ? &fp_plain_kernel<true> : &fp_plain_kernel<false>);
+    if (lds > 65536 - 5 * 1024) {  // beside the static LDS; always the same limit (it is the kernel's, not the launch's)
+      const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 kFpWideMostLdsBytes);
+      if (err != hipSuccess) return static_cast<int>(err);
+    }
     hipLaunchKernelGGL(kernel, grid, block, lds, st, gc, run, fb, ts, vol, q, vstride, scale,
                        static_cast<int>(fixed_sums));
   } else {

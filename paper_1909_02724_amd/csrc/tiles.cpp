@@ -90,8 +90,11 @@ TileShape tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& 
 // 64-bit 8.2, 8.8 at 25; 32-bit 7.9-8.4, 11-12 at 1, 9 or 15 mod 16). Sized
 // at the back-projector's bytes an entry, twice these, one view's tile always
 // fits. Where that leaves none, or its staging slots too few for a mirrored
-// tile, a tile in up to kFpWideLdsBytes (three workgroups a CU) still takes
-// the adds off the global atomics: the wide kernel.
+// tile, the wide kernel still takes the adds off the global atomics, in tiles
+// of 64-bit sums: as many views as three workgroups a CU hold, else one view at
+// up to one workgroup a CU. (60^3 from 20 views at 2 pixels a voxel and a wide
+// cone, one workgroup a CU: 960 us direct, 186 with FP32 sums in half the
+// bytes, 55 so.)
 TileShape fp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& run,
                         const ViewBatch& vb, bool direct) {
   const bool mirror = run.mirror != 0;
@@ -102,8 +105,11 @@ TileShape fp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRu
   ts.wide = ts.vc == 0;
   while (ts.tvp % 16 != 3 && ts.tvp % 16 != 5 && ts.tvp % 16 != 11 && ts.tvp % 16 != 13) ts.tvp += 2;
   const int64_t per_view = static_cast<int64_t>(ts.tu + 1) * ts.tvp * fp_entry_bytes(mirror);
-  ts.vc = static_cast<int32_t>(std::min<int64_t>(
-      kMaxStageViews, (ts.wide ? kFpWideLdsBytes : kTileLdsBytes) / per_view));
+  const int64_t views = !ts.wide                             ? kTileLdsBytes / per_view
+                        : 2 * per_view <= kFpWideLdsBytes     ? kFpWideLdsBytes / (2 * per_view)
+                        : 2 * per_view <= kFpWideMostLdsBytes ? 1
+                                                              : 0;
+  ts.vc = static_cast<int32_t>(std::min<int64_t>(kMaxStageViews, views));
   return ts;
 }
 

@@ -1,0 +1,60 @@
+"""What the entry points launch: kernels, grids, workgroup sizes and LDS, planned
+on the host with the HIP runtime replaced (tests/launch_recorder.cpp)."""
+import os
+import shutil
+import subprocess
+from types import SimpleNamespace
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    import paper_1909_02724_amd as fdk
+    fdk.lib()  # fails where the library is not built
+    exe = str(tmp_path_factory.mktemp("launches") / "launch_recorder")
+    cmd = [HIPCC, "-std=c++17", "-O1", "--offload-arch=gfx950", "--cuda-host-only", "-x", "hip",
+           os.path.join(ROOT, "tests", "launch_recorder.cpp"), "-x", "none", fdk.LIB_PATH,
+           "-Wl,-rpath," + os.path.dirname(fdk.LIB_PATH), "-rdynamic", "-ldl", "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def run(*calls):
+        """Each call: (op, nx, ny, nz, nu, nv, sod, mag, pu, pv, off_v, views)."""
+        r = subprocess.run([exe, *(str(x) for c in calls for x in c)], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        out = SimpleNamespace(launches=[], attrs=[], calls=[])
+        for line in r.stdout.splitlines():
+            kind, name, *rest = line.split()
+            if kind == "attr":
+                out.attrs.append((name, int(rest[0])))
+                continue
+            f = {k: [int(x) for x in v.split(",")] for k, v in (p.split("=") for p in rest)}
+            f = {k: v[0] if len(v) == 1 else v for k, v in f.items()}
+            (out.launches if kind == "launch" else out.calls).append(SimpleNamespace(name=name, **f))
+        assert len(out.calls) == len(calls) and all(c.status == 0 for c in out.calls)
+        return out
+
+    return run
+
+
+def cube(op, n, pixels=1.0, cone=7.8, off_v=0.0, views=20, rows=None):
+    """n^3 voxels, `pixels` a voxel along u and `rows` along v, sod of cone * n."""
+    rows = pixels if rows is None else rows
+    return (op, n, n, n, int(1.2 * n * pixels) + 4, int(1.2 * n * rows) + 4, cone * n, 2.0, 2.0 / pixels,
+            2.0 / rows, off_v, views)
+
+
+def test_wide_adjoint_tiles_hold_64_bit_sums(record):
+    """Every tile of the adjoint's wide kernel has room for a view's 64-bit sums,
+    16 bytes a pixel and its mirror or 8 a pixel."""
+    calls = [cube("fp", 60, px, cone, ov) for px in (1.33, 1.6, 2.0, 2.3, 2.6, 3.0, 3.5, 4.0)
+             for ov in (0.0, 0.27) for cone in (3.0, 7.8)]
+    wide = [f for f in record(*calls).launches if f.name.startswith("fp_wide")]
+    assert len(wide) >= 10
+    for f in wide:
+        view = (f.tu + 1) * f.tvp * (16 if f.mirror else 8)
+        assert f.vc >= 1 and view <= f.lds <= 154 * 1024, f
