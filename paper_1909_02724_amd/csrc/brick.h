@@ -230,6 +230,17 @@ __host__ __device__ inline float slots_at_row(float dvk, int32_t bz) {
   return fminf(static_cast<float>(bz), floorf(2.0f / dvk) + 2.0f);
 }
 
+// Scale of a view's fixed-point sums, as a fraction of the integers' range: 1
+// over the bound km on a pixel's sum (which carries 1 % for the rounding of this
+// and of the sums). Not rounded to a power of two, which would leave up to a bit
+// of the range unused.
+__host__ __device__ inline float sum_scale(float km) {
+  if (!(km > 0.0f)) return 0.0f;
+  int e;
+  const float m = frexpf(fmaxf(km, 0x1p-126f), &e);
+  return ldexpf(rcp_f32(m), -e);
+}
+
 struct BrickCoords {
   int32_t i_lo, i_hi, j_lo, j_hi, i, j, t0, kb;
   float txf, tyf;

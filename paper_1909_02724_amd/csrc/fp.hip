@@ -119,14 +119,17 @@ __device__ __forceinline__ void load_voxels(const GeoConst& gc, const SliceRun& 
 // columns' pixels gave the exact maximum, at two more barriers and column
 // setups a stage and LDS atomics that all lanes send to a few addresses:
 // 16.3 ms, of which 14.0 remained without it at 512^3 from 128 views).
-// S = 2^(31 - e) with 1.01 K M < 2^e
-// keeps every partial sum, rounding included, inside int32. S is a power of
-// two, so the scaling is exact and cannot overflow however small or large
-// the values. A pixel's quantisation error is at most half a unit,
-// 2^(e - 32) ~ K M 2^-31, per contribution (one unit for splats above 2^23
+// S = 2^31 / (1.01 K M) keeps every partial sum, rounding included, inside
+// int32 (sum_scale; the voxels are scaled by a power of two to magnitudes below
+// 1 first, so that it cannot overflow however small or large the values). A
+// pixel's quantisation error is at most half a unit, about K M 2^-32, per
+// contribution (one unit for splats above 2^23
 // units, whose FP32 value is coarser than that anyway): relative to the
 // brick's largest splat, not to the pixel's own sum, which is why
-// wide-range bricks take 64 bits or FP32.
+// wide-range bricks take 64 bits or FP32. (Rounded to a power of two, S wastes
+// half a bit on average, and K's slack of 1.2 lost up to a bit more: a volume
+// of one voxel in 500 at 1 and the rest at 2e-4 then projected with an error
+// of 2.10e-6 against 64 bits, 2.01e-6 by the histogram's K, 1.84e-6 so.)
 constexpr int kFpWideRangeLog2 = 13;        // "small" voxels: below 2^-13 of the brick's max
 constexpr int kFpWideRangePct = 1;          // wide-range path above 1 % small voxels
 constexpr int kFp64RangeLog2 = 40;          // 64-bit fixed point up to this magnitude range
@@ -238,7 +241,10 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
                                               float scale, int fixed_sums) {
   extern __shared__ __attribute__((aligned(16))) int atile[];
   __shared__ BrickView bvs[kMaxViewsPerLaunch];
-  __shared__ float kw[kMaxViewsPerLaunch];  // 1.01 K times the largest W of the brick's columns
+  // 1.01 K times the largest W of the brick's columns; then the view's sum_scale,
+  // and what a unit of its sums is worth.
+  __shared__ float kw[kMaxViewsPerLaunch];
+  __shared__ double units[kMaxViewsPerLaunch];
   __shared__ uint32_t amax_bits, amin_bits, n_nonzero, n_small, nonfinite;
   const int32_t tid = threadIdx.x;
   constexpr int BZ = MIRROR ? kBrickZ : kPlainBrickZ;  // slices per brick
@@ -344,6 +350,15 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
       x[t] = ldexpf(x[t], -ex_max);
       xm[t] = ldexpf(xm[t], -ex_max);
     }
+    if (tid >= v_lo && tid < v_hi) {
+      const float sum = sum_scale(kw[tid] * amax_1);
+      int e;
+      const float m = frexpf(sum, &e);
+      double inv = rcp_f32(m);
+      inv = fma(fma(-static_cast<double>(m), inv, 1.0), inv, inv);  // 1 / m to 2^-46
+      units[tid] = sum > 0.0f ? ldexp(fixed64 ? 1.0 : inv, ex_max - e - (fixed64 ? 62 : 31)) : 0.0;
+      kw[tid] = sum;
+    }
   }
   const int32_t tuf = ts.tu + 1, tv = ts.tv, tvp = ts.tvp;
   const int32_t slot = tuf * tvp;
@@ -368,15 +383,15 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
                  : column_f32(bvs[s0 + sl], bc.txf, bc.tyf, kvf);
         const uint32_t nu = min(c.nu, static_cast<uint32_t>(ts.tu - 1));
         if (!fp32_path) {
-          const float km = kw[s0 + sl] * amax_1;
-          if (!(km > 0.0f)) continue;  // nothing reaches this view (uniform)
-          int e;
-          frexpf(km, &e);
+          const float sum = kw[s0 + sl];
+          if (!(sum > 0.0f)) continue;  // nothing reaches this view (uniform)
           const float du0 = 1.0f - c.du;
           if (WIDE || fixed64) {
-            // S = 2^(63 - e), applied to W x (at most M) so that no
-            // intermediate overflows.
-            const int sh = 63 - e;
+            // S = 2^sh, at most 2^63 of that scale, applied to W x (at most M)
+            // so that no intermediate overflows.
+            int e;
+            frexpf(sum, &e);
+            const int sh = 62 + e;
             if constexpr (MIRROR) {
               uint64_t* const base =
                   reinterpret_cast<uint64_t*>(atile) + 2 * (sl * slot + nu * tvp + c.nvb);
@@ -425,11 +440,10 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
             }
             continue;
           }
-          const float ws = ldexpf(c.w, 31 - e);  // W S, S = 2^(31 - e)
+          // W S, with the weights of the pixel columns u and u + 1.
+          const float ws = c.w * sum * 0x1p31f, v0 = ws * du0, v1 = ws * c.du;
           if (WALK && __builtin_amdgcn_readfirstlane(bvs[s0 + sl].inside)) {
-            // Blocks of kWalk slices, the lane's first one first; weights of
-            // the pixel columns u and u + 1 with the scale folded in.
-            const float v0 = ws * du0, v1 = ws * c.du;
+            // Blocks of kWalk slices, the lane's first one first.
             const float down = fminf(static_cast<float>(kWalk - 1) * c.eps, 0.0f);
 #pragma unroll
             for (int p = 0; p < BZ / kWalk; ++p) {
@@ -468,13 +482,12 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
               uint32_t dn;
               float fr;
               voxel_row_off(c.fvb, c.dvk, static_cast<int32_t>((t + rot) & (kBrickZ - 1)), &dn, &fr);
-              const float val = ws * x[t], vm = ws * xm[t];
-              const float wa = val * (1.0f - fr), wb = val * fr;
-              const float ma = vm * (1.0f - fr), mb = vm * fr;
-              add_pair(base + dn, wa * du0, ma * du0);
-              add_pair(base1 + dn, wa * c.du, ma * c.du);
-              add_pair(base + dn + 1, wb * du0, mb * du0);
-              add_pair(base1 + dn + 1, wb * c.du, mb * c.du);
+              const float fa = 1.0f - fr;
+              const float a0 = v0 * x[t], a1 = v1 * x[t], m0 = v0 * xm[t], m1 = v1 * xm[t];
+              add_pair(base + dn, a0 * fa, m0 * fa);
+              add_pair(base1 + dn, a1 * fa, m1 * fa);
+              add_pair(base + dn + 1, a0 * fr, m0 * fr);
+              add_pair(base1 + dn + 1, a1 * fr, m1 * fr);
             }
             continue;
           }
@@ -485,24 +498,22 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
             uint32_t dn;
             float fr;
             voxel_row_off(c.fvb, c.dvk, static_cast<int32_t>((t + rot) & (kBrickZ - 1)), &dn, &fr);
-            const float val = ws * x[t];
-            const float wa = val * (1.0f - fr), wb = val * fr;
-            atomicAdd(base + dn, fixed_round(wa * du0));
-            atomicAdd(base1 + dn, fixed_round(wa * c.du));
-            atomicAdd(base + dn + 1, fixed_round(wb * du0));
-            atomicAdd(base1 + dn + 1, fixed_round(wb * c.du));
+            const float fa = 1.0f - fr, a0 = v0 * x[t], a1 = v1 * x[t];
+            atomicAdd(base + dn, fixed_round(a0 * fa));
+            atomicAdd(base1 + dn, fixed_round(a1 * fa));
+            atomicAdd(base + dn + 1, fixed_round(a0 * fr));
+            atomicAdd(base1 + dn + 1, fixed_round(a1 * fr));
             {
               // The brick's upper 16 slices, into the same plane.
               uint32_t dn2;
               float fr2;
               voxel_row_off(c.fvb, c.dvk,
                             kBrickZ + static_cast<int32_t>((t + rot) & (kBrickZ - 1)), &dn2, &fr2);
-              const float v2 = ws * xm[t];
-              const float a2 = v2 * (1.0f - fr2), b2 = v2 * fr2;
-              atomicAdd(base + dn2, fixed_round(a2 * du0));
-              atomicAdd(base1 + dn2, fixed_round(a2 * c.du));
-              atomicAdd(base + dn2 + 1, fixed_round(b2 * du0));
-              atomicAdd(base1 + dn2 + 1, fixed_round(b2 * c.du));
+              const float fa2 = 1.0f - fr2, b0 = v0 * xm[t], b1 = v1 * xm[t];
+              atomicAdd(base + dn2, fixed_round(b0 * fa2));
+              atomicAdd(base1 + dn2, fixed_round(b1 * fa2));
+              atomicAdd(base + dn2 + 1, fixed_round(b0 * fr2));
+              atomicAdd(base1 + dn2 + 1, fixed_round(b1 * fr2));
             }
           }
         } else {
@@ -535,13 +546,8 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
         const int32_t s = s0 + sl;
         const int32_t gu = bvs[s].org_u + sc;
         const bool on = static_cast<uint32_t>(gu) < static_cast<uint32_t>(gc.nu);
-        // One fixed-point unit is 2^unit (unused on the FP32 path).
-        int unit = 0;
-        if (!fp32_path) {
-          int e;
-          frexpf(kw[s] * amax_1, &e);
-          unit = e + ex_max - (fixed64 ? 63 : 31);
-        }
+        // In FP64, so that a pixel's sum is rounded once (unused on the FP32 path).
+        const double unit = units[s];
         float* qs = q + fb.idx[s] * vstride + gu;
         for (int32_t r = sr; r < tv; r += rstep) {
           const int32_t at = sl * slot + sc * tvp + r;
@@ -555,10 +561,10 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
             }
           } else if (fixed64) {
             int64_t* const w = reinterpret_cast<int64_t*>(atile) + (MIRROR ? 2 * at : at);
-            ex = static_cast<float>(ldexp(static_cast<double>(w[0]), unit));
+            ex = static_cast<float>(static_cast<double>(w[0]) * unit);
             w[0] = 0;
             if (MIRROR) {
-              ey = static_cast<float>(ldexp(static_cast<double>(w[1]), unit));
+              ey = static_cast<float>(static_cast<double>(w[1]) * unit);
               w[1] = 0;
             }
           } else if (MIRROR) {
@@ -568,10 +574,10 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
             *p = 0;
             const int32_t lo = static_cast<int32_t>(static_cast<uint32_t>(w));
             const int32_t hi = static_cast<int32_t>((w - static_cast<uint64_t>(static_cast<int64_t>(lo))) >> 32);
-            ex = ldexpf(static_cast<float>(lo), unit);
-            ey = ldexpf(static_cast<float>(hi), unit);
+            ex = static_cast<float>(lo * unit);
+            ey = static_cast<float>(hi * unit);
           } else {
-            ex = ldexpf(static_cast<float>(atile[at]), unit);
+            ex = static_cast<float>(atile[at] * unit);
             atile[at] = 0;
           }
           const int32_t gr = bvs[s].org_v + r;
@@ -687,7 +693,7 @@ int launch_forward_project(const GeoConst& gc, const SliceRun& run, const FpBatc
         ts.wide ? (run.mirror ? &fp_wide_kernel<true> : &fp_wide_kernel<false>)
         : run.mirror ? (ts.span >= kWalk ? &fp_mirror_kernel<true> : &fp_mirror_kernel<false>)
                      : (ts.span >= kWalk ? &fp_plain_kernel<true> : &fp_plain_kernel<false>);
-    if (lds > 65536 - 5 * 1024) {  // beside the static LDS; always the same limit (it is the kernel's, not the launch's)
+    if (lds > 65536 - 6 * 1024) {  // beside the static LDS; always the same limit (it is the kernel's, not the launch's)
       const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  kFpWideMostLdsBytes);
