@@ -136,7 +136,12 @@ TileShape fp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRu
 // 78 views: 1.37 -> 1.27 ms, 406 x 245 x 313 from 132: 1.71 general, 1.76
 // staged at the wider pitch, 1.57), and else the general kernel (400^3, wide
 // cone: 4.0 ms, staged 4.1; 371 x 412 x 350: 4.62, 5.45, 4.49 with bricks of 8
-// slices, which lose 10 % at 333 x 367 x 311 from 31 views).
+// slices, which lose 10 % at 333 x 367 x 311 from 31 views). Tiles too small for
+// the five-wave staged kernel's passes (about 0.8 pixels a voxel and less) gain
+// nothing from the four-wave one unless they walk or share views, and run the
+// general kernel, five waves and two views a barrier (300^3 plain from 25 views
+// at 0.5 pixels a voxel 217 us general, 236 staged; 138 x 206 x 320 BF16 from 3
+// views 16.4, 22.4).
 TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& run,
                         const ViewBatch& vb, bool direct) {
   const int32_t entry = run.mirror ? kTileEntryBytes : kPlainEntryBytes;
@@ -178,6 +183,11 @@ TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRu
   ts.groups = bricks(ts) <= kCus ? kMaxGroups : 2 * bricks(ts) <= 3 * kCus ? 2 : 1;
   while (ts.groups > 1 && (ts.groups > vb.nviews || lds(ts, ts.groups) > kGroupLdsBytes))
     ts.groups /= 2;
+  if (ts.span == 0 && ts.groups == 1 && ts.np == kBrickZ && ts.vc == kBpStageViews && !ts.wide &&
+      ts.rows < stage_passes(run.mirror, 0)) {
+    ts.groups = 0;
+    return ts;
+  }
   ts.lds_bytes = lds(ts, ts.groups);
   ts.wide = ts.wide || ts.groups > 1 || ts.np != kBrickZ || ts.vc != kBpStageViews ||
             ts.rows != stage_passes(run.mirror, 0);

@@ -58,3 +58,13 @@ def test_wide_adjoint_tiles_hold_64_bit_sums(record):
     for f in wide:
         view = (f.tu + 1) * f.tvp * (16 if f.mirror else 8)
         assert f.vc >= 1 and view <= f.lds <= 154 * 1024, f
+
+
+@pytest.mark.parametrize("pixels, off_v, name", [
+    (0.5, 0.0, "bp_tiled_kernel<float,_true>"), (0.5, 0.27, "bp_tiled_kernel<float,_false>"),
+    (0.7, 0.27, "bp_tiled_kernel<float,_false>"), (0.75, 0.0, "bp_staged_kernel<float,_true,_4>"),
+    (1.0, 0.0, "bp_staged_kernel<float,_true,_8>"), (1.0, 0.27, "bp_staged_kernel<float,_false,_8>")])
+def test_small_tiles_without_a_walk_run_the_general_kernel(record, pixels, off_v, name):
+    """Below the five-wave staged kernel's passes there is only its four-wave
+    relative, slower there than the general one."""
+    assert [f.name for f in record(cube("bp", 300, pixels, off_v=off_v, views=25)).launches] == [name]
