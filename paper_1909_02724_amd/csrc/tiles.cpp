@@ -87,7 +87,10 @@ TileShape tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRun& 
 // pixel and plane (main, plus mirror for mirrored runs). The column pitch is
 // padded to 3, 5, 11 or 13 mod 16 words, which spreads lanes in neighbouring
 // columns and rows over the banks (modelled clocks per wave instruction:
-// 64-bit 8.2, 8.8 at 25; 32-bit 7.9-8.4, 11-12 at 1, 9 or 15 mod 16). Sized
+// 64-bit 8.2, 8.8 at 25; 32-bit 7.9-8.4, 11-12 at 1, 9 or 15 mod 16), but not
+// where that costs the second view and with it the room for a view's 64-bit
+// sums (148 x 176 x 132 plain from 8 views at 2.12 pixels a voxel, magnitudes
+// over 2^22: 851 us with FP32 sums, 105 so). Sized
 // at the back-projector's bytes an entry, twice these, one view's tile always
 // fits. Where that leaves none, or its staging slots too few for a mirrored
 // tile, the wide kernel still takes the adds off the global atomics, in tiles
@@ -103,8 +106,14 @@ TileShape fp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRu
                             mirror ? kPrefetchSlots : std::numeric_limits<int32_t>::max(), direct);
   if (direct || ts.rstep == 0) return ts;
   ts.wide = ts.vc == 0;
+  const int32_t narrow = ts.tvp;
   while (ts.tvp % 16 != 3 && ts.tvp % 16 != 5 && ts.tvp % 16 != 11 && ts.tvp % 16 != 13) ts.tvp += 2;
-  const int64_t per_view = static_cast<int64_t>(ts.tu + 1) * ts.tvp * fp_entry_bytes(mirror);
+  auto view_bytes = [&](int32_t pitch) {
+    return static_cast<int64_t>(ts.tu + 1) * pitch * fp_entry_bytes(mirror);
+  };
+  if (!ts.wide && 2 * view_bytes(ts.tvp) > kTileLdsBytes && 2 * view_bytes(narrow) <= kTileLdsBytes)
+    ts.tvp = narrow;
+  const int64_t per_view = view_bytes(ts.tvp);
   const int64_t views = !ts.wide                             ? kTileLdsBytes / per_view
                         : 2 * per_view <= kFpWideLdsBytes     ? kFpWideLdsBytes / (2 * per_view)
                         : 2 * per_view <= kFpWideMostLdsBytes ? 1

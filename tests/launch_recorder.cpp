@@ -7,8 +7,8 @@
 //   (VIEWS views of NV rows of NU pixels)
 // Prints, a line each:
 //   attr KERNEL BYTES                        the LDS limit set for a kernel
-//   launch KERNEL grid=X,Y block=N lds=BYTES [of forward projections: tu= tvp=
-//       vc= wide= mirror= rot=A,B]
+//   launch KERNEL grid=X,Y block=N lds=BYTES [of forward projections: tu= tv=
+//       tvp= vc= wide= mirror= rot=A,B]
 //   call OP status=S trig=N                  sines and cosines taken
 #include <hip/hip_runtime_api.h>
 
@@ -105,8 +105,8 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
     const auto& run = *static_cast<fdk::SliceRun*>(args[1]);
     const auto& fb = *static_cast<fdk::FpBatch*>(args[2]);
     const auto& ts = *static_cast<fdk::TileShape*>(args[3]);
-    std::printf(" tu=%d tvp=%d vc=%d wide=%d mirror=%d rot=%d,%d", ts.tu, ts.tvp, ts.vc, ts.wide,
-                run.mirror, fb.rot_a, fb.rot_b);
+    std::printf(" tu=%d tv=%d tvp=%d vc=%d wide=%d mirror=%d rot=%d,%d", ts.tu, ts.tv, ts.tvp, ts.vc,
+                ts.wide, run.mirror, fb.rot_a, fb.rot_b);
   }
   std::printf("\n");
   return hipSuccess;

@@ -68,3 +68,15 @@ def test_small_tiles_without_a_walk_run_the_general_kernel(record, pixels, off_v
     """Below the five-wave staged kernel's passes there is only its four-wave
     relative, slower there than the general one."""
     assert [f.name for f in record(cube("bp", 300, pixels, off_v=off_v, views=25)).launches] == [name]
+
+
+def test_pitch_leaves_room_for_64_bit_sums(record):
+    """A 32-bit tile of the adjoint is padded for the banks only where two views
+    (the room of one view's 64-bit sums) still fit, if they fit without."""
+    calls = [cube("fp", n, px, cone, ov, views=8) for n in (100, 160) for cone in (5.0, 9.1)
+             for ov in (0.0, 0.27) for px in (0.9, 1.0, 1.1, 1.2, 1.9, 2.0, 2.05, 2.1, 2.12, 2.15, 2.2, 2.3)]
+    tiled = [f for f in record(*calls).launches if f.name.startswith("fp_") and not f.wide and f.vc > 0]
+    fit = [f for f in tiled if 2 * (f.tu + 1) * (f.tv | 1) * (8 if f.mirror else 4) <= 36352]
+    assert len(tiled) >= 30 and len(fit) >= 20
+    for f in fit:
+        assert f.vc >= 2, f
