@@ -131,7 +131,7 @@ std::vector<int32_t> adjoint_order(const double* angles, int32_t nviews) {
 }
 
 // Views order[0, n) as one launch of at most kMaxViewsPerLaunch: chunks of one
-// direction each, of at most `chunk` views. FDK_FP_ROT=a,b forces the slot
+// direction each, of at most `chunk` views, in adjoint_order's order. FDK_FP_ROT=a,b forces the slot
 // rotation of the kernels that take one slice at a time (a tuning aid).
 // Returns whether it does.
 bool adjoint_batch(const double* angles, const int32_t* order, int32_t n, int32_t chunk,
@@ -143,18 +143,15 @@ bool adjoint_batch(const double* angles, const int32_t* order, int32_t n, int32_
   fb->rot_b = forced ? b : 4;
   fb->vb.nviews = n;
   fb->nchunks = 0;
-  for (int32_t s = 0; s < n;) {
-    const bool across = rays_along_x(angles[order[s]]);
-    int32_t run = 1;
-    while (s + run < n && rays_along_x(angles[order[s + run]]) == across) ++run;
-    const int32_t parts = (run + chunk - 1) / chunk;
-    for (int32_t p = 0; p < parts; ++p) {
-      fb->first[fb->nchunks] = static_cast<int16_t>(s + run * p / parts);
-      fb->across[fb->nchunks++] = across;
-    }
-    s += run;
+  int32_t turn = 0;  // first view along x
+  while (turn < n && !rays_along_x(angles[order[turn]])) ++turn;
+  for (const auto& [lo, hi] : {std::pair{0, turn}, std::pair{turn, n}}) {
+    fb->across_from = fb->nchunks;
+    const int32_t parts = (hi - lo + chunk - 1) / chunk;
+    for (int32_t p = 0; p < parts; ++p)
+      fb->first[fb->nchunks++] = static_cast<uint8_t>(lo + (hi - lo) * p / parts);
   }
-  fb->first[fb->nchunks] = static_cast<int16_t>(n);
+  fb->first[fb->nchunks] = static_cast<uint8_t>(n);
   for (int32_t s = 0; s < n; ++s) {
     fb->idx[s] = order[s];
     fdk::set_view(&fb->vb, s, angles[order[s]]);
@@ -170,13 +167,18 @@ bool adjoint_batch(const double* angles, const int32_t* order, int32_t n, int32_
 // least: a chunk's views come one after the other (48^3 from 30 views 29.7 ->
 // 19.0 us, 64^3 from 64 29.0 -> 24.9, 60 x 70 x 80 from 16 26.9 -> 18.0;
 // shorter chunks on larger grids lose: 128^3 from 20 views, 768 workgroups of
-// eight views, 44 us, 1280 of four 53).
+// eight views, 44 us, 1280 of four 53). And one where that makes at most two
+// workgroups a CU: a view of a brick that sums in 64 bits or FP32 takes up to 40
+// us (30 x 34 x 16 from 8 views: in 32 bits 17 us two at a time, 12 one, in 64
+// bits 37 and 22, in FP32 92 and 50).
 constexpr int64_t kFpGrid = 4096;
 constexpr int64_t kFpChunkViews = 8;
 int32_t adjoint_chunk(int64_t bricks, int32_t nviews) {
   const int64_t chunks = std::max<int64_t>(1, (kFpGrid + bricks - 1) / bricks);
-  const int64_t least =
-      std::min(kFpChunkViews, std::max<int64_t>(fdk::kFpLeastViews, bricks * nviews / (2 * fdk::kCus)));
+  const int64_t a_view = bricks * nviews;  // workgroups with a view each
+  const int64_t least = a_view <= 2 * fdk::kCus
+                            ? 1
+                            : std::min(kFpChunkViews, std::max<int64_t>(2, a_view / (2 * fdk::kCus)));
   return static_cast<int32_t>(std::max(least, (nviews + chunks - 1) / chunks));
 }
 

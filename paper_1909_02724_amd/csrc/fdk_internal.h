@@ -68,16 +68,15 @@ struct ViewBatch {
 
 // Views of an adjoint launch: view s is projection idx[s] of the call. Chunk c,
 // the blockIdx.y of a workgroup, takes views [first[c], first[c + 1]), whose
-// rays run closer to y than to x if across[c] is 0, else closer to x: groups
+// rays run closer to y than to x up to chunk across_from, then closer to x: groups
 // of 16 threads then run along x or y, across the rays. rot_a, rot_b: see
 // slot_rotation (fp.hip).
-constexpr int kFpLeastViews = 2;  // of a chunk, but for the last of a direction
-constexpr int kMaxChunks = kMaxViewsPerLaunch / kFpLeastViews + 2;  // one direction after the other
+constexpr int kMaxChunks = kMaxViewsPerLaunch;
 struct FpBatch {
   ViewBatch vb;
   int32_t idx[kMaxViewsPerLaunch];
-  int32_t nchunks, rot_a, rot_b;
-  int16_t first[kMaxChunks + 1], across[kMaxChunks];
+  int32_t nchunks, across_from, rot_a, rot_b;
+  uint8_t first[kMaxChunks + 1];
 };
 
 // Bricked back-projection: a workgroup of 256 threads owns a brick of

@@ -41,7 +41,7 @@ __device__ __forceinline__ void splat(float* __restrict__ qs, int32_t nu, int32_
 // 32-bit ones 32 lanes at a time; lanes of such a group that add to one bank
 // take turns, and to one address twice over (measured: m lanes on one
 // address take 2m - 1 turns). Lanes along a ray share a detector column, so
-// groups of 16 run across the rays (FpBatch::across), and each lane starts its
+// groups of 16 run across the rays (FpBatch), and each lane starts its
 // 16 slots at another one, so that lanes that share a column all the same are
 // on different rows: at (a in + b (out mod 4)) mod 16, with `in` the lane's
 // place in its group and `out` the group's.
@@ -251,7 +251,8 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
   // blockIdx.y picks this workgroup's chunk of the launch's views.
   const ViewBatch& vb = fb.vb;
   const int32_t v_lo = fb.first[blockIdx.y], v_hi = fb.first[blockIdx.y + 1];
-  const BrickCoords bc = brick_coords(gc, run, ts, BZ, fb.across[blockIdx.y] != 0);
+  const BrickCoords bc = brick_coords(gc, run, ts, BZ,
+                                      static_cast<int32_t>(blockIdx.y) >= fb.across_from);
   if (tid == 0) {
     amax_bits = n_nonzero = n_small = nonfinite = 0u;
     amin_bits = __float_as_uint(INFINITY);

@@ -80,3 +80,10 @@ def test_pitch_leaves_room_for_64_bit_sums(record):
     assert len(tiled) >= 30 and len(fit) >= 20
     for f in fit:
         assert f.vc >= 2, f
+
+
+@pytest.mark.parametrize("n, views, chunks", [(17, 1, 1), (17, 8, 8), (17, 96, 96), (30, 5, 5), (30, 61, 61), (48, 30, 15)])
+def test_tiny_adjoint_launches_take_a_view_a_workgroup(record, n, views, chunks):
+    """While that makes at most two workgroups a CU; else at least two views."""
+    f, = [f for f in record(cube("fp", n, off_v=0.27, views=views)).launches if f.name.startswith("fp_")]
+    assert f.grid[1] == chunks and (f.grid[0] * views <= 512) == (chunks == views)
