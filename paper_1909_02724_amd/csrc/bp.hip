@@ -753,9 +753,11 @@ int launch_bp_t(const GeoConst& gc, const SliceRun& run, const ViewBatch& vb, co
   const uint64_t nwg = static_cast<uint64_t>(ts.nbx) * ts.nby * ts.nseg;
   const auto kernel = run.mirror ? bp_kernel<T, true>(ts) : bp_kernel<T, false>(ts);
   if (ts.lds_bytes > 65536 - 5 * 1024) {  // beside the static LDS
+    // The limit is the kernel's, not the launch's: always the same, so that a
+    // thread cannot lower it between another's setting and launch.
     const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               ts.lds_bytes);
+                                               kGroupLdsBytes);
     if (err != hipSuccess) return static_cast<int>(err);
   }
   hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>(nwg)), dim3(std::max(ts.groups, 1) * kThreads),

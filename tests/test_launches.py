@@ -87,3 +87,19 @@ def test_tiny_adjoint_launches_take_a_view_a_workgroup(record, n, views, chunks)
     """While that makes at most two workgroups a CU; else at least two views."""
     f, = [f for f in record(cube("fp", n, off_v=0.27, views=views)).launches if f.name.startswith("fp_")]
     assert f.grid[1] == chunks and (f.grid[0] * views <= 512) == (chunks == views)
+
+
+def test_a_kernels_lds_limit_is_the_same_for_every_launch(record):
+    """It belongs to the kernel: a smaller one set by another thread between a
+    launch's setting and the launch would refuse it."""
+    calls = [cube(op, n, px, cone, ov) for op in ("bp", "fp") for n in (20, 40, 64, 90, 128) for ov in (0.0, 0.27)
+             for px in (0.9, 1.0, 1.1, 1.2, 1.7, 2.0) for cone in (3.0, 7.8)]
+    calls += [("filter", 8, 8, 8, nu, 64, 90.0, 2.0, 1.0, 1.0, 0.0, 3) for nu in (3000, 4096, 4200, 6000)]
+    out = record(*calls)
+    limits = {}
+    for name, value in out.attrs:
+        limits.setdefault(name, set()).add(value)
+    assert len(limits) >= 6 and len(out.attrs) >= 60
+    assert all(len(v) == 1 for v in limits.values()), limits
+    for f in out.launches:
+        assert f.lds <= max({65536} | limits.get(f.name, set())), f
