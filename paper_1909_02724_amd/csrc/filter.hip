@@ -5,8 +5,8 @@
 // is diagonal.
 //
 // Short rows are multiplied by the convolution's Toeplitz matrix on the matrix
-// units, in FP64. Rows too long for the FFT tile use a direct convolution: one
-// workgroup per row, the weighted row and the kernel taps in LDS.
+// units, in FP64. Few short rows, and rows too long for the FFT tile, use a direct
+// convolution: one workgroup per row, the weighted row and the kernel taps in LDS.
 //
 // Longer rows use the convolution theorem (Sec. 2.2.3) on the row's first
 // difference and the running sum of the kernel (an identity by summation by
@@ -124,6 +124,14 @@ __global__ __launch_bounds__(kFilterThreads) void filter_direct_kernel(
 // took 1480 us there, 2.56 ms instead of 0.67 for 480000 rows of 160 pixels
 // and 30 instead of 15 for 10000 of 100.
 constexpr int kMatrixRows = 16;
+// Fewer rows and pixels than these take the direct kernel, a row a workgroup: a
+// chain of one weight and one sum a thread, where a workgroup here has 16 rows'
+// weights and 64 dependent products to see through (kernel time, direct and
+// matrix: 16 rows of 256 pixels 6.8 and 15.3 us, 1024 rows 15.4 and 15.7, 2048 27
+// and 18; 512 rows of 160 pixels 6.9 and 11.1, 2048 14.6 and 11.7; 3072 of 64 6.2
+// and 6.0, of 8 4.0 and 4.7, 8192 of 8 6.4 and 4.8).
+constexpr int64_t kMatrixLeastPixels = 1 << 18;
+constexpr int64_t kDirectMostRows = 3072;
 // Below two workgroups a CU the output columns are shared out as well, 64 a
 // workgroup: 1600 rows of 256 pixels 24.8 -> 19.2 us; at the line 45 and 47 us.
 constexpr int64_t kMatrixFewGroups = 2 * kCus;
@@ -799,7 +807,8 @@ int launch_filter_t(const GeoConst& gc, const RowBand& rb, double du, double dv,
         case 12: err = launch_fft<12, OutT, ADJ>(gc, sub, du, dv, sdd, tau, kind, nrows, es, qs, st); break;
         default: err = launch_fft<13, OutT, ADJ>(gc, sub, du, dv, sdd, tau, kind, nrows, es, qs, st); break;
       }
-    } else if (gc.nu <= kMatrixMaxNu) {
+    } else if (gc.nu <= kMatrixMaxNu &&
+               (nrows > kDirectMostRows || nrows * gc.nu >= kMatrixLeastPixels)) {
       err = launch_matrix<OutT, ADJ>(gc, sub, du, dv, sdd, tau, kind, nrows, es, qs, st);
     } else {
       const size_t lds = 2 * static_cast<size_t>(gc.nu) * sizeof(double);

@@ -103,3 +103,11 @@ def test_a_kernels_lds_limit_is_the_same_for_every_launch(record):
     assert all(len(v) == 1 for v in limits.values()), limits
     for f in out.launches:
         assert f.lds <= max({65536} | limits.get(f.name, set())), f
+
+
+@pytest.mark.parametrize("nu, rows, kernel", [
+    (64, 3072, "direct"), (64, 3073, "matrix"), (256, 16, "direct"), (256, 1023, "direct"), (256, 1024, "matrix"),
+    (100, 1, "direct"), (1, 3072, "direct"), (1, 3073, "matrix"), (257, 1, "fft")])
+def test_few_short_rows_are_filtered_directly(record, nu, rows, kernel):
+    f, = record(("filter", 8, 8, 8, nu, 1, 90.0, 2.0, 1.0, 1.0, 0.0, rows)).launches
+    assert f.name.startswith(f"filter_{kernel}_kernel<")
