@@ -9,7 +9,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <limits>
-#include <numeric>
 #include <string>
 #include <utility>
 #include <vector>
@@ -118,44 +117,64 @@ int32_t views_per_launch(int32_t nviews, int32_t cap) {
 
 // Whether a view's rays run closer to x than to y in the lanes' plane: the
 // adjoint's LDS adds are served a group of 16 threads at a time, and threads
-// along a ray share a detector column, so groups run across the rays.
-bool rays_along_x(double beta) { return std::fabs(std::sin(beta)) > std::fabs(std::cos(beta)); }
-
-// Views of a call in the order its adjoint launches take them: by direction.
-std::vector<int32_t> adjoint_order(const double* angles, int32_t nviews) {
-  std::vector<int32_t> order(nviews);
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_partition(order.begin(), order.end(),
-                        [&](int32_t s) { return !rays_along_x(angles[s]); });
-  return order;
+// along a ray share a detector column, so groups run across the rays. (Only the
+// order of the work depends on it. Views on the diagonals go to either side by
+// turns, which splits a whole circle evenly.)
+bool rays_along_x(double beta) {
+  const double half_turns = beta / M_PI, part = half_turns - std::floor(half_turns);
+  return part > 0.25 && part <= 0.75;
 }
 
-// Views order[0, n) as one launch of at most kMaxViewsPerLaunch: chunks of one
-// direction each, of at most `chunk` views, in adjoint_order's order. FDK_FP_ROT=a,b forces the slot
-// rotation of the kernels that take one slice at a time (a tuning aid).
-// Returns whether it does.
-bool adjoint_batch(const double* angles, const int32_t* order, int32_t n, int32_t chunk,
-                   fdk::FpBatch* fb) {
-  int a = 0, b = 0;
-  const char* env = std::getenv("FDK_FP_ROT");
-  const bool forced = env && std::sscanf(env, "%d,%d", &a, &b) == 2;
-  fb->rot_a = forced ? a : 8;
-  fb->rot_b = forced ? b : 4;
-  fb->vb.nviews = n;
+// Views of a call in the order its adjoint launches take them: by direction, one
+// at a time, since a call keeps no list of its views.
+struct AdjointViews {
+  const double* angles;
+  int32_t nviews, next;
+  bool along_x;
+  int32_t take() {  // at most nviews times
+    for (;; ++next) {
+      if (next == nviews) {
+        next = 0;
+        along_x = true;
+      }
+      if (rays_along_x(angles[next]) == along_x) return next++;
+    }
+  }
+  // The next n as one launch; returns how many of them are not along x.
+  int32_t batch(int32_t n, fdk::FpBatch* fb) {
+    int32_t turn = 0;
+    fb->vb.nviews = n;
+    for (int32_t s = 0; s < n; ++s) {
+      const int32_t v = take();
+      fb->idx[s] = v;
+      fdk::set_view(&fb->vb, s, angles[v]);
+      if (!along_x) turn = s + 1;
+    }
+    return turn;
+  }
+};
+
+// Chunks of one direction each, of at most `chunk` views: `turn` views not along
+// x, then the others.
+void cut_chunks(int32_t turn, int32_t chunk, fdk::FpBatch* fb) {
   fb->nchunks = 0;
-  int32_t turn = 0;  // first view along x
-  while (turn < n && !rays_along_x(angles[order[turn]])) ++turn;
-  for (const auto& [lo, hi] : {std::pair{0, turn}, std::pair{turn, n}}) {
+  for (const auto& [lo, hi] : {std::pair{0, turn}, std::pair{turn, fb->vb.nviews}}) {
     fb->across_from = fb->nchunks;
     const int32_t parts = (hi - lo + chunk - 1) / chunk;
     for (int32_t p = 0; p < parts; ++p)
       fb->first[fb->nchunks++] = static_cast<uint8_t>(lo + (hi - lo) * p / parts);
   }
-  fb->first[fb->nchunks] = static_cast<uint8_t>(n);
-  for (int32_t s = 0; s < n; ++s) {
-    fb->idx[s] = order[s];
-    fdk::set_view(&fb->vb, s, angles[order[s]]);
-  }
+  fb->first[fb->nchunks] = static_cast<uint8_t>(fb->vb.nviews);
+}
+
+// Slot rotation of the kernels that take one slice at a time; FDK_FP_ROT=a,b
+// forces one (a tuning aid). Returns whether it does.
+bool adjoint_rotation(fdk::FpBatch* fb) {
+  int a = 0, b = 0;
+  const char* env = std::getenv("FDK_FP_ROT");
+  const bool forced = env && std::sscanf(env, "%d,%d", &a, &b) == 2;
+  fb->rot_a = forced ? a : 8;
+  fb->rot_b = forced ? b : 4;
   return forced;
 }
 
@@ -345,16 +364,16 @@ fdk_status fdk_forward_project(const fdk_geometry* g, int32_t view0, int32_t nvi
       return fail(FDK_ERR_HIP, "zero fill failed: HIP error %d", e);
   }
   fdk::FpBatch fb;
-  const double* const angles = g->angles + view0;
-  const std::vector<int32_t> order = adjoint_order(angles, nviews);
+  const bool forced = adjoint_rotation(&fb);
+  AdjointViews views{g->angles + view0, nviews, 0, false};
   const int32_t per = views_per_launch(nviews, fdk::kMaxViewsPerLaunch);
   for (int32_t b = 0; b < nviews; b += per) {
     const int32_t n = std::min(per, nviews - b);
-    adjoint_batch(angles, order.data() + b, n, n, &fb);
+    const int32_t turn = views.batch(n, &fb);
     for (const fdk::SliceRun& r : sl.runs) {
       fdk::TileShape ts = fdk::fp_tile_shape(g, gc, r, fb.vb, direct);
-      const int64_t bricks = static_cast<int64_t>(ts.nbx) * ts.nby * ts.nseg;
-      if (adjoint_batch(angles, order.data() + b, n, adjoint_chunk(bricks, n), &fb)) ts.span = 0;
+      cut_chunks(turn, adjoint_chunk(static_cast<int64_t>(ts.nbx) * ts.nby * ts.nseg, n), &fb);
+      if (forced) ts.span = 0;
       if (int e = fdk::launch_forward_project(gc, r, fb, ts, vol, q, vstride, scale, fixed_sums,
                                               stream))
         return fail(FDK_ERR_HIP, "forward-projection launch failed: HIP error %d", e);

@@ -2,7 +2,9 @@
 // the HIP runtime, so that an entry point validates, plans and packs as always,
 // and every launch is printed instead of made. Device pointers are never read.
 //
-// Usage: launch_recorder OP NX NY NZ NU NV SOD MAG PU PV OFF_V VIEWS [OP ...]
+// Usage: launch_recorder cap BYTES OP NX NY NZ NU NV SOD MAG PU PV OFF_V VIEWS [OP ...]
+//   BYTES: memory a call may take beyond what is mapped before it (0: any); the
+//   launches of such calls are not printed
 //   OP: bp, fp (back- and forward projection of the whole volume), filter
 //   (VIEWS views of NV rows of NU pixels)
 // Prints, a line each:
@@ -14,6 +16,8 @@
 
 #include <cxxabi.h>
 #include <dlfcn.h>
+#include <sys/resource.h>
+#include <unistd.h>
 
 #include <cstdio>
 #include <cstdlib>
@@ -30,7 +34,7 @@ std::map<const void*, std::string>& names() {
   static std::map<const void*, std::string> m;  // filled before main
   return m;
 }
-long g_trig = 0;
+long g_trig = 0, g_cap = 0;
 struct Config {
   dim3 grid, block;
   size_t lds;
@@ -40,10 +44,22 @@ struct Config {
 double real_trig(const char* name, double x) {
   ++g_trig;
   using Fn = double (*)(double);
-  static std::map<std::string, Fn> fns;
-  Fn& f = fns[name];
+  static Fn fns[2] = {};
+  Fn& f = fns[name[0] == 'c'];
   if (!f) f = reinterpret_cast<Fn>(dlsym(RTLD_NEXT, name));
   return f(x);
+}
+
+// Leaves the process `spare` bytes of address space.
+void limit_memory(long spare) {
+  long pages = 0;
+  if (FILE* f = std::fopen("/proc/self/statm", "r")) {
+    if (std::fscanf(f, "%ld", &pages) != 1) pages = 0;
+    std::fclose(f);
+  }
+  const rlim_t most = static_cast<rlim_t>(pages) * sysconf(_SC_PAGESIZE) + spare;
+  const rlimit limit{most, most};
+  setrlimit(RLIMIT_AS, &limit);
 }
 
 }  // namespace
@@ -99,6 +115,7 @@ hipError_t hipGetSymbolAddress(void** p, const void*) {
   return hipErrorInvalidSymbol;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t) {
+  if (g_cap) return hipSuccess;
   const std::string& name = names()[f];
   std::printf("launch %s grid=%u,%u block=%u lds=%zu", name.c_str(), grid.x, grid.y, block.x, lds);
   if (name.rfind("fp_", 0) == 0) {
@@ -115,7 +132,9 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
 }  // extern "C"
 
 int main(int argc, char** argv) {
-  for (int at = 1; at + 11 < argc; at += 12) {
+  if (argc < 3) return 2;
+  g_cap = std::atol(argv[2]);
+  for (int at = 3; at + 11 < argc; at += 12) {
     const std::string op = argv[at];
     auto i = [&](int n) { return std::atoi(argv[at + n]); };
     auto d = [&](int n) { return std::atof(argv[at + n]); };
@@ -138,6 +157,8 @@ int main(int argc, char** argv) {
     // Far apart, and never read.
     float* const a = reinterpret_cast<float*>(uintptr_t{1} << 40);
     float* const b = reinterpret_cast<float*>(uintptr_t{1} << 50);
+    real_trig("sin", real_trig("cos", 0.0));
+    if (g_cap) limit_memory(g_cap);
     g_trig = 0;
     const int st = op == "bp"   ? fdk_backproject(&g, 0, g.np, a, FDK_F32, b, 0, g.nz, FDK_SLAB_CONTIGUOUS, 1.0f, 0, nullptr)
                    : op == "fp" ? fdk_forward_project(&g, 0, g.np, a, 0, g.nz, FDK_SLAB_CONTIGUOUS, b, 1.0f, 0, nullptr)

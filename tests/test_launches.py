@@ -22,9 +22,10 @@ def record(tmp_path_factory):
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
 
-    def run(*calls):
-        """Each call: (op, nx, ny, nz, nu, nv, sod, mag, pu, pv, off_v, views)."""
-        r = subprocess.run([exe, *(str(x) for c in calls for x in c)], capture_output=True, text=True)
+    def run(*calls, cap=0):
+        """Each call: (op, nx, ny, nz, nu, nv, sod, mag, pu, pv, off_v, views).
+        cap: bytes of memory the calls may take beyond what is mapped before them."""
+        r = subprocess.run([exe, "cap", str(cap), *(str(x) for c in calls for x in c)], capture_output=True, text=True)
         assert r.returncode == 0, r.stderr
         out = SimpleNamespace(launches=[], attrs=[], calls=[])
         for line in r.stdout.splitlines():
@@ -38,6 +39,7 @@ def record(tmp_path_factory):
         assert len(out.calls) == len(calls) and all(c.status == 0 for c in out.calls)
         return out
 
+    run.capped = lambda cap, *calls: run(*calls, cap=cap)
     return run
 
 
@@ -111,3 +113,16 @@ def test_a_kernels_lds_limit_is_the_same_for_every_launch(record):
 def test_few_short_rows_are_filtered_directly(record, nu, rows, kernel):
     f, = record(("filter", 8, 8, 8, nu, 1, 90.0, 2.0, 1.0, 1.0, 0.0, rows)).launches
     assert f.name.startswith(f"filter_{kernel}_kernel<")
+
+
+def test_a_forward_projection_evaluates_each_angle_once(record):
+    """One sine and one cosine a view, whatever the launches and slice runs."""
+    for n, off_v, views in ((17, 0.0, 400), (40, 0.27, 97), (41, 0.0, 96), (130, 0.0, 191)):
+        assert record(cube("fp", n, off_v=off_v, views=views)).calls[0].trig == 2 * views
+
+
+def test_a_forward_projection_allocates_no_memory_for_its_views(record):
+    """No C++ exception may cross the C ABI: with 2^23 views and no memory to
+    spare beyond their angles, the call plans every launch as with few."""
+    out = record.capped(1 << 25, ("fp", 2, 2, 2, 4, 4, 90.0, 2.0, 1.0, 1.0, 0.0, 1 << 23))
+    assert out.calls[0].trig == 2 << 23
