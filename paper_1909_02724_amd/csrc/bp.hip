@@ -692,6 +692,8 @@ void bp_tiled_wide_kernel(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,
                                        bvs);
 }
 
+static_assert(sizeof(BrickView) * kMaxViewsPerLaunch == kBpStaticLdsBytes, "sized for the host's rules");
+
 // Row-walk kernels: the five-wave instance for tiles of kSpanRows passes, and
 // the four-wave one for taller tiles and for several groups of threads a
 // workgroup.

@@ -144,7 +144,9 @@ constexpr int kSmallBrickZ = 4;
 constexpr int kMaxGroups = 4;  // 256-thread groups sharing a brick, each with its own views
 constexpr int kCus = 256;
 constexpr int kResidentGroups = 4 * kCus;   // groups the chip holds at four waves per SIMD
-constexpr int kGroupLdsBytes = 154 * 1024;  // of 160 KB, beside the per-view brick constants
+constexpr int kCuLdsBytes = 160 * 1024;
+constexpr int kGroupLdsBytes = 154 * 1024;  // of these, beside the per-view brick constants
+constexpr int kBpStaticLdsBytes = 48 * kMaxViewsPerLaunch;  // a workgroup's brick constants
 // Staging passes of a view's tile: exactly so many in the five-wave kernel
 // (np = 0), at most so many in the four-wave one with np slices a thread. Each
 // pass costs its branches whether it is taken or not: with 8 and 14 for every

@@ -139,7 +139,9 @@ TileShape fp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRu
 // Tiles of which two do not fit the 35.5 KB of a quarter of a CU's LDS: plain
 // runs take the staged kernel all the same (301 x 277 x 199 at 1.2 pixels a
 // voxel: 2.08 -> 1.69 ms), small mirrored grids bricks of 8 slices (450
-// bricks: 690 us general, 559 at 16 slices, 528 at 8). Large mirrored grids
+// bricks: 690 us general, 559 at 16 slices, 528 at 8), while the chip holds half of
+// those at once (882 bricks, four of the halves a CU: 184 us general, 166 at 8 slices;
+// three a CU, 840 bricks: 191, 210, 945: 27.1, 32.1). Large mirrored grids
 // get a pitch of 3, 7, 9 or 13 mod 16, next to 7 or 9 only, if two tiles then
 // fit (columns five apart may share a bank at 3 and 13; 340 x 347 x 389 from
 // 78 views: 1.37 -> 1.27 ms, 406 x 245 x 313 from 132: 1.71 general, 1.76
@@ -174,14 +176,18 @@ TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRu
   };
   TileShape ts = shape(kBrickZ);
   if (ts.vc <= 0) return ts;
-  const bool few = bricks(ts) <= kResidentGroups;
-  if (few) {
+  // Whether wide tiles halve their bricks: the chip holds half of them at once.
+  const TileShape half = shape(kMidBrickZ);
+  const int64_t per_cu = std::min(4, kCuLdsBytes / (lds(half, 1) + kBpStaticLdsBytes));
+  const bool mid = bricks(ts) <= kResidentGroups && bricks(half) <= 2 * per_cu * kCus;
+  if (bricks(ts) <= kResidentGroups) {
     for (int32_t np : {kMidBrickZ, kSmallBrickZ}) {
       const TileShape t = shape(np);
-      if (staged(t) && (bricks(t) <= kCus || (ts.vc != kBpStageViews && np == kMidBrickZ))) ts = t;
+      if (staged(t) && (bricks(t) <= kCus || (mid && ts.vc != kBpStageViews && np == kMidBrickZ)))
+        ts = t;
     }
   }
-  if (run.mirror && ts.vc != kBpStageViews && !few) {
+  if (run.mirror && ts.vc != kBpStageViews && !mid) {
     TileShape t = ts;
     t.tvp = t.tv | 1;
     while (t.tvp % 16 != 3 && t.tvp % 16 != 7 && t.tvp % 16 != 9 && t.tvp % 16 != 13) t.tvp += 2;

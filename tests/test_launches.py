@@ -126,3 +126,16 @@ def test_a_forward_projection_allocates_no_memory_for_its_views(record):
     spare beyond their angles, the call plans every launch as with few."""
     out = record.capped(1 << 25, ("fp", 2, 2, 2, 4, 4, 90.0, 2.0, 1.0, 1.0, 0.0, 1 << 23))
     assert out.calls[0].trig == 2 << 23
+
+
+@pytest.mark.parametrize("nx, ny, nz, pixels, halved", [
+    (236, 109, 284, 1.9, False), (169, 164, 250, 1.9, False), (229, 118, 214, 1.8, False),
+    (128, 160, 200, 1.9, True), (280, 100, 216, 1.42, True)])
+def test_wide_tiles_halve_their_bricks_while_half_of_them_fit(record, nx, ny, nz, pixels, halved):
+    """Beyond what the chip holds twice over, bricks of 8 slices are slower than
+    the general kernel."""
+    n = max(nx, ny, nz)
+    call = ("bp", nx, ny, nz, int(1.3 * n * pixels), int(1.3 * n * pixels), 6.0 * n, 2.0, 2.0 / pixels,
+            2.0 / pixels, 0.0, 20)
+    f, = record(call).launches
+    assert f.name == ("bp_groups_kernel<float,_true,_0,_8>" if halved else "bp_tiled_wide_kernel<float,_true>"), f
