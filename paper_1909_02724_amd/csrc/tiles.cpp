@@ -177,9 +177,12 @@ TileShape bp_tile_shape(const fdk_geometry* g, const GeoConst& gc, const SliceRu
   TileShape ts = shape(kBrickZ);
   if (ts.vc <= 0) return ts;
   // Whether wide tiles halve their bricks: the chip holds half of them at once.
-  const TileShape half = shape(kMidBrickZ);
-  const int64_t per_cu = std::min(4, kCuLdsBytes / (lds(half, 1) + kBpStaticLdsBytes));
-  const bool mid = bricks(ts) <= kResidentGroups && bricks(half) <= 2 * per_cu * kCus;
+  bool mid = false;
+  if (ts.vc != kBpStageViews && bricks(ts) <= kResidentGroups) {
+    const TileShape half = shape(kMidBrickZ);
+    const int64_t per_cu = std::min(4, kCuLdsBytes / (lds(half, 1) + kBpStaticLdsBytes));
+    mid = bricks(half) <= 2 * per_cu * kCus;
+  }
   if (bricks(ts) <= kResidentGroups) {
     for (int32_t np : {kMidBrickZ, kSmallBrickZ}) {
       const TileShape t = shape(np);
