@@ -62,11 +62,11 @@ LDS_BYTES_PER_CLK = 222.6
 LDS_ATOMIC64_BYTES_PER_CLK = 79.6
 HBM_PEAK = 8.0e12
 # VALU work per voxel-view update of the mirrored row walk over 8 slices: of
-# its 10 rows two u-interpolations each (1 FMA on the staged difference) and
-# two differences to the next row, 38 per 8 voxel pairs; per pair its offset
-# (1 FMA), two clamps, and for the voxel and its mirror two sample FMAs and the
-# weighted accumulate (6): (38 / 8 + 9) / 2 = 6.875 full-rate operations.
-VALU_OPS_PER_UPDATE = 6.875
+# its 10 rows two u-interpolations each (1 FMA on the staged difference), 20 per
+# 8 voxel pairs; per pair its offset (1 FMA) and the offset's sign (1), and for
+# the voxel and its mirror the selected row, its difference, the sample and the
+# weighted accumulate (8): (20 / 8 + 10) / 2 = 6.25 full-rate operations.
+VALU_OPS_PER_UPDATE = 6.25
 LDS_BYTES_PER_UPDATE = 10.0  # 10 rows of 16 bytes (value and u-difference, main and mirror) per 8 pairs
 # The adjoint's row walk (fixed-point tile, a row's and its mirror row's sums
 # in one 64-bit word), in full-rate equivalents: per voxel pair two clamped

@@ -235,55 +235,55 @@ __device__ __forceinline__ void pair_column(const std::conditional_t<MIRROR, flo
   // Accumulator of slice t (plain runs: t < 2 NP); t is a constant after
   // unrolling, so this selects a register.
   auto slice_acc = [&](int t) { return t < NP ? acc + t : accm + (t - NP); };
-          // Reads run one voxel pair ahead of use, so LDS latency overlaps the
-          // previous pair's arithmetic.
-          uint32_t dn;
-          float fr;
-          voxel_row_off(c.fvb, c.dvk, 0, &dn, &fr);
-          if constexpr (MIRROR) {
-            float4 A = reinterpret_cast<const float4*>(pb + dn * kEntry)[0];
-            float4 B = reinterpret_cast<const float4*>(pb + dn * kEntry)[1];
-  #pragma unroll
-            for (int t = 0; t < NP; ++t) {
-              float4 An = A, Bn = B;
-              uint32_t dn1 = 0;
-              float fr1 = 0.0f;
-              if (t + 1 < NP) {
-                voxel_row_off(c.fvb, c.dvk, t + 1, &dn1, &fr1);
-                const float4* p = reinterpret_cast<const float4*>(pb + dn1 * kEntry);
-                An = p[0];
-                Bn = p[1];
-              }
-              const float ta = fmaf(c.du, A.y, A.x), tb = fmaf(c.du, B.y, B.x);
-              acc[t] = fmaf(c.w, fmaf(fr, tb - ta, ta), acc[t]);
-              const float ma = fmaf(c.du, A.w, A.z), mb = fmaf(c.du, B.w, B.z);
-              accm[t] = fmaf(c.w, fmaf(fr, mb - ma, ma), accm[t]);
-              A = An;
-              B = Bn;
-              fr = fr1;
-            }
-          } else {
-            // Rows n and n + 1 are adjacent 8-byte entries: one read2.
-            float2 A = reinterpret_cast<const float2*>(pb + dn * kEntry)[0];
-            float2 B = reinterpret_cast<const float2*>(pb + dn * kEntry)[1];
-  #pragma unroll
-            for (int t = 0; t < BZ; ++t) {
-              float2 An = A, Bn = B;
-              uint32_t dn1 = 0;
-              float fr1 = 0.0f;
-              if (t + 1 < BZ) {
-                voxel_row_off(c.fvb, c.dvk, t + 1, &dn1, &fr1);
-                const float2* p = reinterpret_cast<const float2*>(pb + dn1 * kEntry);
-                An = p[0];
-                Bn = p[1];
-              }
-              const float ta = fmaf(c.du, A.y, A.x), tb = fmaf(c.du, B.y, B.x);
-              *slice_acc(t) = fmaf(c.w, fmaf(fr, tb - ta, ta), *slice_acc(t));
-              A = An;
-              B = Bn;
-              fr = fr1;
-            }
-          }
+  // Reads run one voxel pair ahead of use, so LDS latency overlaps the
+  // previous pair's arithmetic.
+  uint32_t dn;
+  float fr;
+  voxel_row_off(c.fvb, c.dvk, 0, &dn, &fr);
+  if constexpr (MIRROR) {
+    float4 A = reinterpret_cast<const float4*>(pb + dn * kEntry)[0];
+    float4 B = reinterpret_cast<const float4*>(pb + dn * kEntry)[1];
+#pragma unroll
+    for (int t = 0; t < NP; ++t) {
+      float4 An = A, Bn = B;
+      uint32_t dn1 = 0;
+      float fr1 = 0.0f;
+      if (t + 1 < NP) {
+        voxel_row_off(c.fvb, c.dvk, t + 1, &dn1, &fr1);
+        const float4* p = reinterpret_cast<const float4*>(pb + dn1 * kEntry);
+        An = p[0];
+        Bn = p[1];
+      }
+      const float ta = fmaf(c.du, A.y, A.x), tb = fmaf(c.du, B.y, B.x);
+      acc[t] = fmaf(c.w, fmaf(fr, tb - ta, ta), acc[t]);
+      const float ma = fmaf(c.du, A.w, A.z), mb = fmaf(c.du, B.w, B.z);
+      accm[t] = fmaf(c.w, fmaf(fr, mb - ma, ma), accm[t]);
+      A = An;
+      B = Bn;
+      fr = fr1;
+    }
+  } else {
+    // Rows n and n + 1 are adjacent 8-byte entries: one read2.
+    float2 A = reinterpret_cast<const float2*>(pb + dn * kEntry)[0];
+    float2 B = reinterpret_cast<const float2*>(pb + dn * kEntry)[1];
+#pragma unroll
+    for (int t = 0; t < BZ; ++t) {
+      float2 An = A, Bn = B;
+      uint32_t dn1 = 0;
+      float fr1 = 0.0f;
+      if (t + 1 < BZ) {
+        voxel_row_off(c.fvb, c.dvk, t + 1, &dn1, &fr1);
+        const float2* p = reinterpret_cast<const float2*>(pb + dn1 * kEntry);
+        An = p[0];
+        Bn = p[1];
+      }
+      const float ta = fmaf(c.du, A.y, A.x), tb = fmaf(c.du, B.y, B.x);
+      *slice_acc(t) = fmaf(c.w, fmaf(fr, tb - ta, ta), *slice_acc(t));
+      A = An;
+      B = Bn;
+      fr = fr1;
+    }
+  }
 }
 
 template <typename T, bool MIRROR, bool TILED, bool WIDE = false>
@@ -694,9 +694,9 @@ void bp_tiled_wide_kernel(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,
 
 static_assert(sizeof(BrickView) * kMaxViewsPerLaunch == kBpStaticLdsBytes, "sized for the host's rules");
 
-// Row-walk kernels: the five-wave instance for tiles of kSpanRows passes, and
-// the four-wave one for taller tiles and for several groups of threads a
-// workgroup.
+// Staged kernels: the five-wave instance for tiles of exactly its passes
+// (stage_passes), and the four-wave one for other tiles and for several groups
+// of threads a workgroup.
 template <typename T, bool MIRROR, int SPAN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 5)))
 void bp_staged_kernel(GeoConst gc, SliceRun run, ViewBatch vb, TileShape ts,

@@ -44,7 +44,9 @@ __device__ __forceinline__ float tap(const T* __restrict__ qs, int32_t nu, int32
 struct BrickView {
   float uo, vo, au, bu, av, bv, zo, ci, cj;
   int32_t org_u, org_v;
-  int32_t inside;  // the tile (columns org_u .. org_u + tu, its rows and mirror rows) is on the detector
+  // The tile (columns org_u .. org_u + tu, its rows and mirror rows) is on the
+  // detector; in the adjoint, which sums off it too, that its row walk holds.
+  int32_t inside;
 };
 
 // bz: slices per brick; mirror: whether the tile also holds the mirror rows
@@ -198,12 +200,12 @@ __device__ __forceinline__ ColumnF32 column_f64(const GeoConst& gc, const ViewGe
   return c;
 }
 
-// Bounds for the adjoint's fixed-point sums. Most columns of the brick with floor(u) in {p - 1, p} for any p. Along a row
-// of the brick u(i + 1) - u(i) = ku (ai z - a ci)(j) / (z z'), whose numerator
-// depends on j alone and is affine in it, so the smallest spacing follows from
-// the brick's corners; an interval of two pixels then holds at most
-// ceil(2 / spacing) of a row's columns (2.002: rounding of u). Likewise along
-// j; the smaller total holds.
+// Bounds for the adjoint's fixed-point sums. Most columns of the brick with
+// floor(u) in {p - 1, p} for any p. Along a row of the brick
+// u(i + 1) - u(i) = ku (ai z - a ci)(j) / (z z'), whose numerator depends on j
+// alone and is affine in it, so the smallest spacing follows from the brick's
+// corners; an interval of two pixels then holds at most ceil(2 / spacing) of a
+// row's columns (2.002: rounding of u). Likewise along j; the smaller total holds.
 __host__ __device__ inline int32_t columns_at_pixel(const GeoConst& gc, const ViewGeo& g, int32_t i_lo,
                                                     int32_t i_hi, int32_t j_lo, int32_t j_hi) {
   const int32_t ni = i_hi - i_lo + 1, nj = j_hi - j_lo + 1;
