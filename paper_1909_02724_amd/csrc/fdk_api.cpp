@@ -198,7 +198,8 @@ int32_t adjoint_chunk(int64_t bricks, int32_t nviews) {
   const int64_t least = a_view <= 2 * fdk::kCus
                             ? 1
                             : std::min(kFpChunkViews, std::max<int64_t>(2, a_view / (2 * fdk::kCus)));
-  return static_cast<int32_t>(std::max(least, (nviews + chunks - 1) / chunks));
+  return static_cast<int32_t>(
+      std::min<int64_t>(fdk::kFpMostViews, std::max(least, (nviews + chunks - 1) / chunks)));
 }
 
 struct Slab {

@@ -72,6 +72,10 @@ struct ViewBatch {
 // of 16 threads then run along x or y, across the rays. rot_a, rot_b: see
 // slot_rotation (fp.hip).
 constexpr int kMaxChunks = kMaxViewsPerLaunch;
+// Views of a chunk at most: their constants (60 bytes a view) and the tiles share
+// the LDS of a fifth of a CU. (With arrays for 96 views 11 % slower where that
+// cost the fifth workgroup; in dynamic LDS 2 % slower throughout.)
+constexpr int kFpMostViews = 80;
 struct FpBatch {
   ViewBatch vb;
   int32_t idx[kMaxViewsPerLaunch];

@@ -240,17 +240,18 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
                                               float* __restrict__ q, int64_t vstride,
                                               float scale, int fixed_sums) {
   extern __shared__ __attribute__((aligned(16))) int atile[];
-  __shared__ BrickView bvs[kMaxViewsPerLaunch];
+  // Of the chunk's views.
+  __shared__ BrickView bvs[kFpMostViews];
   // 1.01 K times the largest W of the brick's columns; then the view's sum_scale,
   // and what a unit of its sums is worth.
-  __shared__ float kw[kMaxViewsPerLaunch];
-  __shared__ double units[kMaxViewsPerLaunch];
+  __shared__ float kw[kFpMostViews];
+  __shared__ double units[kFpMostViews];
   __shared__ uint32_t amax_bits, amin_bits, n_nonzero, n_small, nonfinite;
   const int32_t tid = threadIdx.x;
   constexpr int BZ = MIRROR ? kBrickZ : kPlainBrickZ;  // slices per brick
   // blockIdx.y picks this workgroup's chunk of the launch's views.
   const ViewBatch& vb = fb.vb;
-  const int32_t v_lo = fb.first[blockIdx.y], v_hi = fb.first[blockIdx.y + 1];
+  const int32_t v_lo = fb.first[blockIdx.y], views = fb.first[blockIdx.y + 1] - v_lo;
   const BrickCoords bc = brick_coords(gc, run, ts, BZ,
                                       static_cast<int32_t>(blockIdx.y) >= fb.across_from);
   if (tid == 0) {
@@ -258,8 +259,9 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
     amin_bits = __float_as_uint(INFINITY);
   }
   const float kvf = static_cast<float>(gc.kv);
-  if (tid >= v_lo && tid < v_hi) {
-    BrickView b = brick_setup(gc, view_geo(gc, vb.sn[tid], vb.cs[tid]), bc.i_lo, bc.i_hi, bc.j_lo,
+  if (tid < views) {
+    const ViewGeo geo = view_geo(gc, vb.sn[v_lo + tid], vb.cs[v_lo + tid]);
+    BrickView b = brick_setup(gc, geo, bc.i_lo, bc.i_hi, bc.j_lo,
                               bc.j_hi, bc.kb, 0, 0, BZ, MIRROR);
     // z is affine in (i, j): W, dv/dk and the drift of v are extremal at corners.
     float w = 0.0f, drift = 0.0f, dvk = INFINITY;
@@ -271,8 +273,7 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
       dvk = fminf(dvk, col.dvk);
     }
     kw[tid] = 1.01f * slots_at_row(dvk, BZ) *
-              static_cast<float>(columns_at_pixel(gc, view_geo(gc, vb.sn[tid], vb.cs[tid]), bc.i_lo,
-                                                  bc.i_hi, bc.j_lo, bc.j_hi)) * w;
+              static_cast<float>(columns_at_pixel(gc, geo, bc.i_lo, bc.i_hi, bc.j_lo, bc.j_hi)) * w;
     b.inside = static_cast<float>(kWalk - 1) * drift <= static_cast<float>(kSpanDrift);  // the walk holds
     bvs[tid] = b;
   }
@@ -351,7 +352,7 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
       x[t] = ldexpf(x[t], -ex_max);
       xm[t] = ldexpf(xm[t], -ex_max);
     }
-    if (tid >= v_lo && tid < v_hi) {
+    if (tid < views) {
       const float sum = sum_scale(kw[tid] * amax_1);
       int e;
       const float m = frexpf(sum, &e);
@@ -369,8 +370,8 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
   for (int32_t e = tid; e < (MIRROR ? 2 : 1) * (WIDE ? 2 : 1) * ts.vc * slot; e += kThreads) atile[e] = 0;
   __syncthreads();
   int* const mtile = atile + ts.vc * slot;
-  for (int32_t s0 = v_lo; s0 < v_hi; s0 += vstep) {
-    const int32_t nvc = min(vstep, v_hi - s0);
+  for (int32_t s0 = 0; s0 < views; s0 += vstep) {
+    const int32_t nvc = min(vstep, views - s0);
     // Main rows in planes [0, vc) and mirror rows in planes [vc, 2 vc), one
     // 32-bit word per pixel: all LDS banks serve the adds (interleaved
     // (main, mirror) pairs reached only half of them and conflicted 10-way).
@@ -380,7 +381,8 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
     if (bc.owner) {
       for (int32_t sl = 0; sl < nvc; ++sl) {
         const ColumnF32 c =
-            WIDE ? column_f64(gc, view_geo(gc, vb.sn[s0 + sl], vb.cs[s0 + sl]), bvs[s0 + sl], bc.i, bc.j, bc.kb)
+            WIDE ? column_f64(gc, view_geo(gc, vb.sn[v_lo + s0 + sl], vb.cs[v_lo + s0 + sl]), bvs[s0 + sl],
+                              bc.i, bc.j, bc.kb)
                  : column_f32(bvs[s0 + sl], bc.txf, bc.tyf, kvf);
         const uint32_t nu = min(c.nu, static_cast<uint32_t>(ts.tu - 1));
         if (!fp32_path) {
@@ -549,7 +551,7 @@ __device__ __forceinline__ void fp_tiled_body(const GeoConst& gc, const SliceRun
         const bool on = static_cast<uint32_t>(gu) < static_cast<uint32_t>(gc.nu);
         // In FP64, so that a pixel's sum is rounded once (unused on the FP32 path).
         const double unit = units[s];
-        float* qs = q + fb.idx[s] * vstride + gu;
+        float* qs = q + fb.idx[v_lo + s] * vstride + gu;
         for (int32_t r = sr; r < tv; r += rstep) {
           const int32_t at = sl * slot + sc * tvp + r;
           float ex, ey = 0.0f;
@@ -694,7 +696,7 @@ int launch_forward_project(const GeoConst& gc, const SliceRun& run, const FpBatc
         ts.wide ? (run.mirror ? &fp_wide_kernel<true> : &fp_wide_kernel<false>)
         : run.mirror ? (ts.span >= kWalk ? &fp_mirror_kernel<true> : &fp_mirror_kernel<false>)
                      : (ts.span >= kWalk ? &fp_plain_kernel<true> : &fp_plain_kernel<false>);
-    if (lds > 65536 - 6 * 1024) {  // beside the static LDS; always the same limit (it is the kernel's, not the launch's)
+    if (lds > 65536 - 5 * 1024) {  // beside the static LDS; always the same limit (it is the kernel's, not the launch's)
       const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  kFpWideMostLdsBytes);
