@@ -197,8 +197,8 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
 // row is summed in a register and added to the tile once per pixel column: 40
 // LDS adds per 16 slices (or pairs) instead of 64, at constant offsets, and
 // 435 VALU instructions a wave and view instead of 600. The kernel stays
-// bound by LDS adds (62 % of the cycles, 43 % of those for lanes that meet)
-// beside VALU issue (48 % at the full rate). 512^3 from 128 views: 15.5 -> 9.4
+// bound by LDS adds (56 % of the cycles, 44 % of those for lanes that meet)
+// beside VALU issue (44 % at the full rate). 512^3 from 128 views: 15.5 -> 9.4
 // ms with the bounds, thread groups and tile pitch above; 215 x 190 x 171 at
 // 1.2 pixels a voxel, which takes one slice at a time: 1.17 -> 0.69 ms.
 //   emit(row, sum, sum of mirrors)
